@@ -101,6 +101,7 @@ struct md_ctx_s {
   double* u0 = nullptr;     // MSD reference, original id order [N][3]
   double* msd_part = nullptr;
   double* msd_out = nullptr;
+  unsigned long long* rdf_hist = nullptr;  // pair counts of md_rdf
   md_obs* log_dev = nullptr;
   int64_t log_cap = 0;
   std::vector<void*> owned;
@@ -1297,9 +1298,19 @@ md_status rdf_with(md_ctx c, int32_t rep, double rmax, int32_t nbins, double* g,
     md_status b = build_all(c);
     if (b) return b;
   }
+  // Longer ranges take more cells to each side while these are distinct
+  // (2 h + 1 <= nc) and built; the number of pairs tested then follows the
+  // range instead of the box.  Unbuilt cells are not built for it: that call
+  // keeps visiting all pairs.  (The margin covers rounding in the cell of a
+  // particle, as the skin test does for h = 1.)
+  int32_t h = by_cells ? 1 : 0;
+  if (!by_cells && c->built)
+    for (int32_t q = 2; 2 * q + 1 <= d.nc && !h; ++q)
+      if (rmax <= (q * (d.L / d.nc) - c->p.skin) * (1.0 - 1e-12)) h = q;
   launch_zero_u64(c->stream, hist, nbins);
-  if (by_cells)
-    launch_rdf_cells(c->stream, d.coff, d.nc, c->cell_start, c->pos, d.L, rmax, nbins, hist);
+  if (h)
+    launch_rdf_cells(c->stream, d.coff, d.nc, h, c->cell_start, c->pos, d.L, c->p.skin, rmax,
+                     nbins, hist);
   else
     launch_rdf(c->stream, c->pos, d.off, d.n, d.L, rmax, nbins, hist);
   HIPCHECK(c, hipGetLastError());
@@ -1332,12 +1343,11 @@ md_status md_rdf(md_ctx c, int32_t rep, double rmax, int32_t nbins, double* g) {
   if (!c) return MD_EINVAL;
   md_status rc = rdf_args(c, rep, rmax, nbins, g);
   if (rc) return rc;
-  unsigned long long* hist = nullptr;
-  rc = dalloc(c, &hist, (size_t)nbins);
-  if (rc) return rc;
-  rc = rdf_with(c, rep, rmax, nbins, g, hist, true);
-  dfree(c, hist);
-  return rc;
+  if (!c->rdf_hist) {  // 64 KiB, kept: an allocation and its release cost more than the counts
+    rc = dalloc(c, &c->rdf_hist, (size_t)kStaticBins);
+    if (rc) return rc;
+  }
+  return rdf_with(c, rep, rmax, nbins, g, c->rdf_hist, true);
 }
 
 md_status md_rdf_static(md_ctx c, int32_t rep, double rmax, int32_t nbins, double* g) {

@@ -346,9 +346,10 @@ void launch_rdf(hipStream_t s, const double4* pos, int32_t off, int32_t n, doubl
 // a[0, n) = 0 (a fill kernel rather than hipMemsetAsync, so callers may
 // capture it in a graph)
 void launch_zero_u64(hipStream_t s, unsigned long long* a, int32_t n);
-void launch_rdf_cells(hipStream_t s, int32_t c0, int32_t nc, const int32_t* cell_start,
-                      const double4* pos, double L, double rmax, int32_t nbins,
-                      unsigned long long* hist);
+// h: cells of the search to each side along an axis, 2 h + 1 <= nc
+void launch_rdf_cells(hipStream_t s, int32_t c0, int32_t nc, int32_t h,
+                      const int32_t* cell_start, const double4* pos, double L, double skin,
+                      double rmax, int32_t nbins, unsigned long long* hist);
 
 // staged path (stage.h, nlist.hip tile mode, force_staged.hip)
 struct RowTile;
