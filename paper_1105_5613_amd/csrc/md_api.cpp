@@ -53,7 +53,9 @@ struct md_ctx_s {
   // staged path (row tiles with LDS-staged neighbourhoods)
   int32_t staged = 0, nrt = 0, lcap_f = 0;
   int32_t cells = 0;  // list-free cell path (row tiles, no neighbour list)
-  int32_t any_single = 0, any_multi = 0;  // replicas with one cell / with >= 3 per side
+  int32_t any_multi = 0;  // some replica has >= 3 cells per side
+  int32_t ntiles1 = 0;    // tiles of the replicas with one cell
+  Tile* tiles1 = nullptr;
   bool small_chain = false;  // one small replica: the one-block rebuild chain
   bool small_list = false;   // ... and the 32-lanes-per-particle list build
   std::vector<RowTile> rtiles_h;
@@ -281,10 +283,10 @@ void run_chain(md_ctx c, hipStream_t s, bool zeroed = false) {
                        c->pos_tmp, c->vel_tmp, c->id_tmp, c->pos, c->vel, c->id, c->xref, c->nbr,
                        c->ncount, c->st, c->pos16);
   else
-    launch_nlist(s, c->ntiles, c->tiles, c->reps, c->rebuild, c->tab, c->thr_form, c->cell_start,
+    launch_nlist(s, c->ntiles1, c->tiles1, c->reps, c->rebuild, c->tab, c->thr_form, c->cell_start,
                  c->stride, c->cap, c->pos_tmp, c->vel_tmp, c->id_tmp, c->pos, c->vel, c->id,
-                 c->xref, c->nbr, c->ncount, c->st, c->ncells, c->cell_rep, c->any_single,
-                 c->any_multi, c->pos16, spread_c);
+                 c->xref, c->nbr, c->ncount, c->st, c->ncells, c->cell_rep, c->any_multi, c->pos16,
+                 spread_c);
 }
 
 // energy: form PE and W (the staged and list-free kernels always do).
@@ -669,9 +671,12 @@ md_status md_init_alloc(md_ctx* out, const md_params* p, int32_t nrep, const int
   bool all3 = true;
   for (const RepDesc& d : c->reps_h) {
     all3 = all3 && d.nc >= 3;
-    if (d.nc == 1) c->any_single = 1;
-    else c->any_multi = 1;
+    if (d.nc != 1) c->any_multi = 1;
   }
+  std::vector<Tile> tiles1;
+  for (const Tile& t : c->tiles_h)
+    if (c->reps_h[t.rep].nc == 1) tiles1.push_back(t);
+  c->ntiles1 = (int32_t)tiles1.size();
   if ((p->path == MD_PATH_STAGED || p->path == MD_PATH_CELLS) && !all3) {
     delete c;
     return fail(nullptr, MD_EINVAL, "the staged and cell paths need >= 3 cells per box side");
@@ -796,6 +801,7 @@ md_status md_init_alloc(md_ctx* out, const md_params* p, int32_t nrep, const int
   }
   ALLOC(c->reps, (size_t)nrep);
   ALLOC(c->tiles, (size_t)c->ntiles);
+  if (c->ntiles1) ALLOC(c->tiles1, (size_t)c->ntiles1);
   ALLOC(c->tab, 1);
   ALLOC(c->st, 1);
   ALLOC(c->cell_rep, (size_t)c->ncells);
@@ -866,6 +872,7 @@ md_status md_init_alloc(md_ctx* out, const md_params* p, int32_t nrep, const int
   }
   bool ok = up(c->reps, c->reps_h.data(), sizeof(RepDesc) * nrep) &&
             up(c->tiles, c->tiles_h.data(), sizeof(Tile) * c->ntiles) &&
+            (!c->ntiles1 || up(c->tiles1, tiles1.data(), sizeof(Tile) * tiles1.size())) &&
             up(c->tab, &tab, sizeof(PairTab)) &&
             up(c->cell_rep, cell_rep.data(), sizeof(int32_t) * c->ncells) &&
             up(c->lam, ones.data(), sizeof(double) * nrep) &&

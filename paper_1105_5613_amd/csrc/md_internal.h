@@ -231,13 +231,14 @@ inline int32_t fma_pair_form(const double* t, int32_t ntypes) {
 }
 // nlist.hip.  thr_form: fma_pair_form of the list thresholds.  spread: 0, or
 // the number of consecutive cells whose blocks share an XCD (see xcd_spread).
-void launch_nlist(hipStream_t s, int32_t ntiles, const Tile* tiles, const RepDesc* reps,
+// tiles1: the tiles of the one-cell replicas.
+void launch_nlist(hipStream_t s, int32_t ntiles1, const Tile* tiles1, const RepDesc* reps,
                   const int32_t* rebuild, const PairTab* tab, int32_t thr_form,
                   const int32_t* cell_start, int32_t stride, int32_t cap,
                   const double4* pos_tmp, const double* vel_tmp, const int32_t* id_tmp,
                   double4* pos, double* vel, int32_t* id, double* xref,
                   uint32_t* nbr, int32_t* ncount, DevState* st, int32_t ncells,
-                  const int32_t* cell_rep, int32_t any_single, int32_t any_multi,
+                  const int32_t* cell_rep, int32_t any_multi,
                   int4* pos16, int32_t spread);
 // The gather-path search of a one-replica context with at most
 // kSmallListN particles and >= 3 cells per side: the rows of launch_nlist

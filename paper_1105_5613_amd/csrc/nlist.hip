@@ -47,8 +47,17 @@ __device__ inline int32_t cell_coord(double c, double inv_cell, int32_t nc) {
 }
 
 // One-cell boxes (nc = 1): every other particle of the replica is tested
-// with the minimum image  d - L nearbyint(d / L).
-__global__ __launch_bounds__(kTile) void k_nlist(
+// with the minimum image  d - L nearbyint(d / L).  One wave per home
+// particle: the lanes take 64 consecutive partners at a time, and a hit's
+// row is the count so far plus the hits on the lanes below it, so a row holds
+// its partners in index order.  Positions are wrapped into [0, L), so the
+// quotient d / L lies in (-1, 1) and rounds to +-1 exactly when |d| > L / 2
+// (the next double above L / 2 divides to a quotient above 1/2; the tie
+// d = L / 2 rounds to 0), and no division is needed.  The box holds a few
+// hundred particles, so the time is latency: 500 particles took 156 us with
+// one thread per particle, 7.1 us with one wave.
+constexpr int kOneWaves = 4;  // home particles per block
+__global__ __launch_bounds__(64 * kOneWaves) void k_nlist(
     const Tile* __restrict__ tiles, const RepDesc* __restrict__ reps,
     const int32_t* __restrict__ rebuild, const PairTab* __restrict__ tab, int32_t stride,
     int32_t cap, const double4* __restrict__ pos_tmp, const double* __restrict__ vel_tmp,
@@ -59,35 +68,43 @@ __global__ __launch_bounds__(kTile) void k_nlist(
   if (!st->any_rebuild) return;
   if (threadIdx.x < 16) s_thr[threadIdx.x] = tab->thr[threadIdx.x];
   __syncthreads();
-  const Tile t = tiles[xcd_block(blockIdx.x, gridDim.x)];
+  constexpr int32_t kBlocks = kTile / kOneWaves;  // blocks per tile
+  const Tile t = tiles[blockIdx.x / kBlocks];
   if (!rebuild[t.rep]) return;
-  const int32_t i = t.start + threadIdx.x;
+  const int lane = threadIdx.x & 63;
+  const int32_t i = t.start + (int32_t)(blockIdx.x % kBlocks) * kOneWaves +
+                    __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (i >= t.end) return;
   const RepDesc R = reps[t.rep];
-  if (R.nc != 1) return;  // cell grids: k_nlist_cells
   const double4 p = pos_tmp[i];
   const int32_t ti = (int32_t)p.w;
   const double* thr = &s_thr[ti * 4];
+  const double half = 0.5 * R.L;
   int32_t cnt = 0;
   uint32_t* out = nbr + list_base(i, cap);
-  for (int32_t j = R.off; j < R.off + R.n; ++j) {
-    if (j == i) continue;
-    const double4 q = pos_tmp[j];
+  for (int32_t j0 = R.off; j0 < R.off + R.n; j0 += 64) {
+    const int32_t j = j0 + lane;
+    const bool valid = (j < R.off + R.n) & (j != i);
+    const double4 q = pos_tmp[valid ? j : i];
     double ex = q.x - p.x, ey = q.y - p.y, ez = q.z - p.z;
-    double kx = rint(ex / R.L), ky = rint(ey / R.L), kz = rint(ez / R.L);
-    double tx = R.L * kx, ty = R.L * ky, tz = R.L * kz;
-    ex = ex - tx;
-    ey = ey - ty;
-    ez = ez - tz;
-    double r2 = (ex * ex + ey * ey) + ez * ez;
-    if (r2 < thr[(int32_t)q.w]) {
+    const int32_t kx = ex > half ? 1 : (ex < -half ? -1 : 0),
+                  ky = ey > half ? 1 : (ey < -half ? -1 : 0),
+                  kz = ez > half ? 1 : (ez < -half ? -1 : 0);
+    ex = ex - R.L * (double)kx;
+    ey = ey - R.L * (double)ky;
+    ez = ez - R.L * (double)kz;
+    const double r2 = (ex * ex + ey * ey) + ez * ez;
+    const bool hit = valid & (r2 < thr[(int32_t)q.w]);
+    const uint64_t m = __builtin_amdgcn_ballot_w64(hit);
+    const int32_t row = cnt + __popcll(m & ((1ull << lane) - 1ull));
+    if (hit && row < cap) {
       // image s = -k; with one cell d = -s nc = k
-      const int32_t sx = -(int32_t)kx, sy = -(int32_t)ky, sz = -(int32_t)kz;
-      const uint32_t code = dcode ? image_code(-sx, -sy, -sz) : image_code(sx, sy, sz);
-      if (cnt < cap) out[(size_t)cnt * kSlice] = (uint32_t)j | code;
-      ++cnt;
+      const uint32_t code = dcode ? image_code(kx, ky, kz) : image_code(-kx, -ky, -kz);
+      out[(size_t)row * kSlice] = (uint32_t)j | code;
     }
+    cnt += __popcll(m);
   }
+  if (lane != 0) return;
   ncount[i] = cnt;
   if (cnt > cap) atomicOr(&st->err, kErrOverflow);
   // the new cell order becomes the live state; the list is built on it
@@ -105,7 +122,6 @@ __global__ __launch_bounds__(kTile) void k_nlist(
   vel[2 * (size_t)stride + i] = vel_tmp[2 * (size_t)stride + i];
   id[i] = id_tmp[i];
 }
-
 
 // One wave per home cell (nc >= 3), in two phases per group of at most
 // kCwGroup home particles.
@@ -554,13 +570,13 @@ __global__ __launch_bounds__(64 * kCwWaves) void k_nlist_cells(
 
 }  // namespace
 
-void launch_nlist(hipStream_t s, int32_t ntiles, const Tile* tiles, const RepDesc* reps,
+void launch_nlist(hipStream_t s, int32_t ntiles1, const Tile* tiles1, const RepDesc* reps,
                   const int32_t* rebuild, const PairTab* tab, int32_t thr_form,
                   const int32_t* cell_start, int32_t stride, int32_t cap,
                   const double4* pos_tmp, const double* vel_tmp, const int32_t* id_tmp,
                   double4* pos, double* vel, int32_t* id, double* xref, uint32_t* nbr,
                   int32_t* ncount, DevState* st, int32_t ncells, const int32_t* cell_rep,
-                  int32_t any_single, int32_t any_multi, int4* pos16, int32_t spread) {
+                  int32_t any_multi, int4* pos16, int32_t spread) {
   // mixed lists (records present) carry cell offsets instead of images
   const int32_t dcode = pos16 != nullptr;
   if (any_multi) {
@@ -573,9 +589,10 @@ void launch_nlist(hipStream_t s, int32_t ntiles, const Tile* tiles, const RepDes
     if (thr_form == 2) KN(2); else KN(4);
 #undef KN
   }
-  if (any_single)
-    k_nlist<<<ntiles, kTile, 0, s>>>(tiles, reps, rebuild, tab, stride, cap, pos_tmp, vel_tmp,
-                                     id_tmp, pos, vel, id, xref, nbr, ncount, st, dcode, pos16);
+  if (ntiles1)
+    k_nlist<<<ntiles1 * (kTile / kOneWaves), 64 * kOneWaves, 0, s>>>(
+        tiles1, reps, rebuild, tab, stride, cap, pos_tmp, vel_tmp, id_tmp, pos, vel, id, xref,
+        nbr, ncount, st, dcode, pos16);
 }
 
 void launch_nlist_tiles(hipStream_t s, int32_t ncells, const int32_t* cell_rep,
