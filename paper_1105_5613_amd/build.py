@@ -24,9 +24,10 @@ COMMON = ["-O3", "-std=c++17", f"--offload-arch={ARCH}", "-fPIC", "-x", "hip",
           "-Wall", "-Werror", "-Wno-unused-command-line-argument",
           "-I", os.path.join(HERE, "..", "include")]
 PER_FILE = {"nlist.hip": ["-ffp-contract=off"], "nlist_small.hip": ["-ffp-contract=off"],
-            "analysis.hip": ["-ffp-contract=off"]}
-SOURCES = ["cells.hip", "nlist.hip", "nlist_small.hip", "force.hip", "force_staged.hip", "force_cells.hip",
-           "integrate.hip", "analysis.hip", "md_api.cpp"]
+            "nlist_brick.hip": ["-ffp-contract=off", "-fno-honor-nans"], "analysis.hip": ["-ffp-contract=off"]}
+SOURCES = ["cells.hip", "nlist.hip", "nlist_small.hip", "nlist_brick.hip", "force.hip",
+           "force_brick.hip", "force_staged.hip", "force_cells.hip", "integrate.hip",
+           "analysis.hip", "md_api.cpp"]
 
 
 def _compile(src: str) -> str:

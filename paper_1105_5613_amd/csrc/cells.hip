@@ -8,7 +8,7 @@
 // to the cell segments, and a per-cell rank sort by original id that makes
 // the order deterministic, followed by a gather of the particle records into
 // the new order.
-#include "md_internal.h"
+#include "brick.h"
 
 namespace mdk {
 namespace {
@@ -378,16 +378,27 @@ __global__ __launch_bounds__(kTile) void k_scatter(const Tile* __restrict__ tile
 }
 
 // One wave per cell: rank the cell's particles by original id (ids are
-// unique) and gather their records to cell_start + rank.
+// unique) and gather their records to cell_start + rank.  On the brick path
+// the blocks from nbc on tabulate the rows of the tiles, one wave per tile.
 __global__ __launch_bounds__(256) void k_cell_gather(
     int32_t ncells, const int32_t* __restrict__ cell_rep, const int32_t* __restrict__ rebuild,
     const int32_t* __restrict__ cell_start, const int32_t* __restrict__ tmp_src, int32_t stride,
     const int32_t* __restrict__ id, const double4* __restrict__ pos,
     const double* __restrict__ vel, int32_t* __restrict__ id_tmp, double4* __restrict__ pos_tmp,
-    double* __restrict__ vel_tmp, const DevState* __restrict__ st) {
+    double* __restrict__ vel_tmp, DevState* st, int32_t nbc, const RepDesc* __restrict__ reps,
+    BrickArgs A) {
   if (!st->any_rebuild) return;
-  const int32_t c = blockIdx.x * 4 + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
+  if ((int32_t)blockIdx.x >= nbc) {
+    const int32_t t = ((int32_t)blockIdx.x - nbc) * 4 + (threadIdx.x >> 6);
+    if (t >= A.ntiles) return;
+    const BrickTile T = A.tiles[t];
+    if (rebuild[T.rep])
+      tile_rows(T, reps[T.rep], cell_start, lane, A.slots, A.head + t, A.row + (size_t)t * A.rows,
+                A.hrow + (size_t)t * A.hrows, st);
+    return;
+  }
+  const int32_t c = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (c >= ncells) return;
   if (!rebuild[cell_rep[c]]) return;
   const int32_t s = cell_start[c], n = cell_start[c + 1] - s;
@@ -444,7 +455,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_chain_small(
     double4* __restrict__ pos, const int32_t* __restrict__ id, int32_t* __restrict__ img,
     int32_t* __restrict__ cell_start, int32_t stride, const double* __restrict__ vel,
     int32_t* __restrict__ id_tmp, double4* __restrict__ pos_tmp, double* __restrict__ vel_tmp,
-    DevState* st) {
+    DevState* st, BrickArgs A) {
   constexpr int kPer = kSmallN / kSmallThreads;
   __shared__ int32_t s_start[kSmallCells + 1];  // counts, then first particle of each cell
   __shared__ __align__(16) int32_t s_id[kSmallN];  // ids by cell, then slot
@@ -512,6 +523,9 @@ __global__ __launch_bounds__(kSmallThreads) void k_chain_small(
   if (t == 0) s_start[ncl] = tot;
   __syncthreads();
   for (int32_t c = t; c <= ncl; c += kSmallThreads) cell_start[R.coff + c] = s_start[c];
+  for (int32_t b = w; b < A.ntiles; b += kSmallThreads / 64)  // brick path: rows of the tiles
+    tile_rows(A.tiles[b], R, s_start - R.coff, lane, A.slots, A.head + b,
+              A.row + (size_t)b * A.rows, A.hrow + (size_t)b * A.hrows, st);
 #pragma unroll
   for (int u = 0; u < kPer; ++u)
     if (R.off + t + u * kSmallThreads < end) s_id[s_start[cl[u]] - R.off + sl[u]] = idv[u];
@@ -579,6 +593,12 @@ void launch_relayout_list(hipStream_t s, int32_t ntot, const int32_t* ncount, in
         ntot, ncount, cap_old, cap_new, (const uint32_t*)src, (uint32_t*)dst);
 }
 
+void launch_relayout_chunks(hipStream_t s, int32_t ntot, const int32_t* nchunk, int32_t cap_old,
+                            int32_t cap_new, const uint4* src, uint4* dst) {
+  k_relayout_list<uint4><<<nblk(ntot, 256), 256, 0, s>>>(ntot, nchunk, cap_old, cap_new, src,
+                                                         dst);
+}
+
 void launch_mark_rebuild(hipStream_t s, int32_t nrep, int32_t* rebuild, DevState* st) {
   k_mark_rebuild<<<nblk(nrep, 256), 256, 0, s>>>(nrep, rebuild, st);
 }
@@ -621,19 +641,21 @@ void launch_scatter(hipStream_t s, int32_t ntiles, const Tile* tiles, const int3
 void launch_chain_small(hipStream_t s, const RepDesc* reps, const int32_t* rebuild,
                         double4* pos, const int32_t* id, int32_t* img, int32_t* cell_start,
                         int32_t stride, const double* vel, int32_t* id_tmp, double4* pos_tmp,
-                        double* vel_tmp, DevState* st) {
+                        double* vel_tmp, DevState* st, const BrickArgs& bricks) {
   k_chain_small<<<1, kSmallThreads, 0, s>>>(reps, rebuild, pos, id, img, cell_start, stride,
-                                            vel, id_tmp, pos_tmp, vel_tmp, st);
+                                            vel, id_tmp, pos_tmp, vel_tmp, st, bricks);
 }
 
 void launch_cell_gather(hipStream_t s, int32_t ncells, const int32_t* cell_rep,
                         const int32_t* rebuild, const int32_t* cell_start,
                         const int32_t* tmp_src, int32_t stride, const int32_t* id,
                         const double4* pos, const double* vel, int32_t* id_tmp,
-                        double4* pos_tmp, double* vel_tmp, const DevState* st) {
-  k_cell_gather<<<nblk(ncells, 4), 256, 0, s>>>(ncells, cell_rep, rebuild, cell_start, tmp_src,
-                                                stride, id, pos, vel, id_tmp, pos_tmp, vel_tmp,
-                                                st);
+                        double4* pos_tmp, double* vel_tmp, DevState* st, const RepDesc* reps,
+                        const BrickArgs& bricks) {
+  const int32_t nbc = (int32_t)nblk(ncells, 4);
+  k_cell_gather<<<nbc + nblk(bricks.ntiles, 4), 256, 0, s>>>(
+      ncells, cell_rep, rebuild, cell_start, tmp_src, stride, id, pos, vel, id_tmp, pos_tmp,
+      vel_tmp, st, nbc, reps, bricks);
 }
 
 }  // namespace mdk

@@ -8,8 +8,10 @@
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <type_traits>
 #include <vector>
 
+#include "brick.h"
 #include "md_internal.h"
 #include "stage.h"
 
@@ -53,6 +55,16 @@ struct md_ctx_s {
   // staged path (row tiles with LDS-staged neighbourhoods)
   int32_t staged = 0, nrt = 0, lcap_f = 0;
   int32_t cells = 0;  // list-free cell path (row tiles, no neighbour list)
+  // brick path (brick.h): what MD_PATH_AUTO runs where it can (plan_bricks)
+  bool brick = false;
+  std::vector<BrickTile> btiles_h;
+  std::vector<Brick> bricks_h;
+  BrickArgs ba{};
+  BrickPair bp_h{};
+  BrickPair* bp = nullptr;
+  int32_t brick_parts = 0;   // partials of the force kernel
+  double brick_homes = 0.0;  // expected home particles of the fullest tile
+  int32_t brick_extra = 0;   // list chunks beyond the capacity's (one per pass but the first)
   int32_t any_multi = 0;  // some replica has >= 3 cells per side
   int32_t ntiles1 = 0;    // tiles of the replicas with one cell
   Tile* tiles1 = nullptr;
@@ -111,7 +123,7 @@ struct md_ctx_s {
   // captured K-step graphs (md_params.graph_steps)
   hipStream_t cap_stream = nullptr;
   hipGraphExec_t gexec = nullptr;
-  int64_t gkey[15] = {0};
+  int64_t gkey[16] = {0};
   int32_t prof_epoch = 0;
   // force-kernel timing
   int32_t prof_every = 0;
@@ -258,7 +270,7 @@ void run_chain(md_ctx c, hipStream_t s, bool zeroed = false) {
   if (c->small_chain) {
     // its histogram lives in LDS: nothing to clear
     launch_chain_small(s, c->reps, c->rebuild, c->pos, c->id, c->img, c->cell_start, c->stride,
-                       c->vel, c->id_tmp, c->pos_tmp, c->vel_tmp, c->st);
+                       c->vel, c->id_tmp, c->pos_tmp, c->vel_tmp, c->st, c->ba);
   } else {
     if (!zeroed) launch_zero_counts(s, c->ncells, c->cell_rep, c->rebuild, c->st, c->counts);
     launch_bin(s, c->ntiles, c->tiles, c->reps, c->rebuild, c->pos, c->id, c->img, c->counts,
@@ -268,9 +280,13 @@ void run_chain(md_ctx c, hipStream_t s, bool zeroed = false) {
                    c->tmp_src, c->st, spread_t);
     launch_cell_gather(s, c->ncells, c->cell_rep, c->rebuild, c->cell_start, c->tmp_src,
                        c->stride, c->id, c->pos, c->vel, c->id_tmp, c->pos_tmp, c->vel_tmp,
-                       c->st);
+                       c->st, c->reps, c->ba);
   }
-  if (c->cells)
+  if (c->brick)
+    launch_nlist_brick(s, c->ba, c->p.ntypes, c->reps, c->rebuild, c->tab, c->cell_start,
+                       c->stride, c->cap, c->bp_h, c->pos_tmp, c->vel_tmp, c->id_tmp, c->pos,
+                       c->vel, c->id, c->xref, c->ncount, c->st, spread_c);
+  else if (c->cells)
     launch_commit_order(s, c->ntiles, c->tiles, c->rebuild, c->stride, c->pos_tmp, c->vel_tmp,
                         c->id_tmp, c->pos, c->vel, c->id, c->xref, c->st);
   else if (c->staged)
@@ -289,12 +305,25 @@ void run_chain(md_ctx c, hipStream_t s, bool zeroed = false) {
                  spread_c);
 }
 
+// Threads of a brick force block: the expected homes of the fullest tile with
+// some room, at least four waves (which share the copy to LDS) and at most
+// eight, of which three blocks run per CU; with no more blocks than CUs each
+// has its CU to itself and takes sixteen for the copy.
+int32_t brick_threads(md_ctx c) {
+  const int32_t want = (int32_t)std::ceil(1.1 * c->brick_homes * c->tpp / 64.0) * 64;
+  return c->ba.ntiles * c->ba.split <= 256 ? kBrickThreads : std::max(256, std::min(want, 512));
+}
+
 // energy: form PE and W (the staged and list-free kernels always do).
 // mode 2 (gather path only): the fused NVE step, see FuseOut; the caller
 // swaps the position buffers after the launch.
 void launch_forces(md_ctx c, int32_t mode, hipStream_t s, int32_t energy = 1,
                    int32_t nzero = 0) {
-  if (c->cells)
+  if (c->brick)
+    launch_force_brick(s, c->mixed, mode, energy, c->tpp, brick_threads(c), c->bp_h.four, c->ba,
+                       c->reps, c->tab, c->bp, c->pos, c->vel, c->frc, c->stride, c->p.dt,
+                       c->part, c->st, FuseOut{c->pos_tmp, nullptr, c->xref, c->counts, nzero});
+  else if (c->cells)
     launch_force_cells(s, c->mixed, mode, c->rc2_form, c->nrt, c->rtiles, c->reps, c->tab,
                        c->cell_start, c->pos, c->vel, c->frc, c->stride, c->p.dt, c->part,
                        c->st);
@@ -310,6 +339,177 @@ void launch_forces(md_ctx c, int32_t mode, hipStream_t s, int32_t energy = 1,
                  FuseOut{c->pos_tmp, c->pos16_alt, c->xref, c->counts, nzero});
 }
 
+// Constants of the brick force kernel from the pair table.  The two-species
+// form needs base + 2 d = value bit for bit for every constant, with the base
+// taken for one species throughout; that holds for one of the two choices
+// unless the constants are very uneven, and then (as with more species) the
+// kernel reads a table.
+BrickPair brick_pair(const md_params& p, const PairTab& t) {
+  BrickPair b{};
+  b.mk = p.potential == MD_POT_SOFT ? 0.0f : 0.5f;
+  double smin = p.sig[0];
+  for (int a = 0; a < p.ntypes; ++a)
+    for (int q = 0; q < p.ntypes; ++q) smin = std::min(smin, p.sig[a * MD_MAXT + q]);
+  b.tiny = 1e-30 * smin * smin;  // (smin^2 / tiny)^7 is an ordinary double
+  b.four = 1;
+  if (p.ntypes > 2) return b;
+  for (int32_t flip = p.ntypes == 1 ? 1 : 0; flip < 2; ++flip) {
+    bool exact = true;
+    auto split = [&](auto (&out)[2], double base, double value) {
+      using V = std::remove_reference_t<decltype(out[0])>;
+      const V lo = (V)base, v = (V)value;
+      const V d = (v - lo) * (V)0.5;
+      out[0] = lo;
+      out[1] = d;
+      exact = exact && std::fma(d, (V)2.0, lo) == v;
+    };
+    for (int a = 0; a < p.ntypes; ++a) {
+      // species 1 - flip: bit clear; species flip: bit set (absent with one species)
+      const int k0 = a * MD_MAXT + (1 - flip), k1 = p.ntypes == 1 ? k0 : a * MD_MAXT + flip;
+      auto s6 = [&](int k) { return t.sig2[k] * t.sig2[k] * t.sig2[k]; };
+      split(b.rc2[a], t.rc2[k0], t.rc2[k1]);
+      split(b.a[a], t.f12[k0] * (s6(k0) * s6(k0)), t.f12[k1] * (s6(k1) * s6(k1)));
+      split(b.b[a], t.f6[k0] * s6(k0), t.f6[k1] * s6(k1));
+      split(b.fs[a], t.fs[k0], t.fs[k1]);
+      split(b.msig2[a], t.sig2[k0], t.sig2[k1]);
+      split(b.mf12[a], t.f12[k0], t.f12[k1]);
+      split(b.mfs[a], t.fs[k0], t.fs[k1]);
+    }
+    if (exact) {
+      b.flip = flip;
+      b.four = 0;
+      return b;
+    }
+  }
+  b.flip = 0;
+  return b;
+}
+
+// Whether the context takes the brick path, and its tiles and bricks.
+// Conditions: MD_PATH_AUTO with no force variant asked for by tpp or unroll
+// (those name gather variants), at least three cells per side in every
+// replica, parameters whose r^-12 coefficient is an ordinary double, and in
+// every replica 27 cells that fit the LDS slots.
+//
+// Tiles: the most home cells (up to 4 per axis) whose expected neighbourhood
+// fits the slots with 12 % to spare and whose homes fit one or two rounds of
+// a block (240), as the copy to LDS is paid per neighbourhood cell.  (Cells
+// between 2.8 and 3 wide hold 26 to 32 particles: 2 x 2 x 2 of them need up to
+// 2,350 slots, hence the larger LDS layout.)  The rule
+// looks at the density of one replica only, so that a replica's sums are the
+// same alone and in a batch.
+bool plan_bricks(md_ctx c) {
+  const md_params& p = c->p;
+  if (p.path != MD_PATH_AUTO || p.tpp != 0 || p.unroll != 0) return false;
+  for (int a = 0; a < p.ntypes; ++a)
+    for (int b = 0; b < p.ntypes; ++b) {
+      const double s = p.sig[a * MD_MAXT + b], e = std::fabs(p.eps[a * MD_MAXT + b]);
+      if (s < 1e-15 || s > 1e15 || (e != 0.0 && (e < 1e-60 || e > 1e60))) return false;
+    }
+  auto slots = [](double ppc, int x, int y, int z) {
+    return 1.12 * ppc * (x + 2) * (y + 2) * (z + 2) + 48.0;
+  };
+  for (const RepDesc& d : c->reps_h) {
+    if (d.nc < 3) return false;
+    // short lists: the copy of the neighbourhood is not earned back (the
+    // soft-sphere box, 15 entries: 57 us by gathers, 96 by bricks)
+    const double side = max_rc(p) + p.skin;
+    if ((double)d.n / d.volume * 4.0 / 3.0 * M_PI * side * side * side < 48.0) return false;
+    if (slots((double)d.n / ((double)d.nc * d.nc * d.nc), 1, 1, 1) >= kBrickSlotsBig) return false;
+  }
+  c->btiles_h.clear();
+  c->bricks_h.clear();
+  c->brick_parts = 0;
+  c->ba = BrickArgs{};
+  bool big = false;
+  for (int32_t r = 0; r < c->nrep; ++r) {
+    RepDesc& d = c->reps_h[r];
+    const int32_t nc = d.nc;
+    const double ppc = (double)d.n / ((double)nc * nc * nc);
+    auto per = [&](int t) { return (int64_t)(nc + t - 1) / t; };
+    int bx = 1, by = 1, bz = 1;
+    for (int x = 1; x <= std::min(4, nc); ++x)
+      for (int y = 1; y <= x; ++y)
+        for (int z = 1; z <= y; ++z) {
+          const double homes = ppc * x * y * z;
+          if (homes > 240.0 || slots(ppc, x, y, z) >= kBrickSlotsBig) continue;
+          const int v = x * y * z, bv = bx * by * bz;
+          const int h = (x + 2) * (y + 2) * (z + 2), bh = (bx + 2) * (by + 2) * (bz + 2);
+          if (v > bv || (v == bv && h < bh)) bx = x, by = y, bz = z;
+        }
+    if (slots(ppc, bx, by, bz) >= kBrickSlots) big = true;
+    // bricks of a tile: the matrix product takes 32 homes at a time against
+    // 64 candidates; three chunks' worth of time per brick go elsewhere
+    int hx = 1, hy = 1, hz = 1;
+    double best = 1e300;
+    for (int x = 1; x <= bx; ++x)
+      for (int y = 1; y <= by; ++y)
+        for (int z = 1; z <= bz; ++z) {
+          const double homes = ppc * x * y * z, cand = ppc * (x + 2) * (y + 2) * (z + 2);
+          const double cost = (std::ceil(cand * 1.02 / 64.0) + 3.0) *
+                              std::ceil(1.08 * homes / 32.0) / homes;
+          if (cost < best) best = cost, hx = x, hy = y, hz = z;
+        }
+    const double cand = ppc * (hx + 2) * (hy + 2) * (hz + 2);
+    c->ba.groups = std::max(c->ba.groups,
+                            (int32_t)std::ceil(1.15 * ppc * hx * hy * hz / 32.0));
+    c->brick_extra = std::max(c->brick_extra, (int32_t)(1.15 * cand / nlist_brick_pass()));
+    d.fb0 = c->brick_parts;
+    auto cut = [](int32_t n, int32_t parts, int32_t k) {
+      return (int32_t)((int64_t)n * k / parts);
+    };
+    const int32_t ntx = (int32_t)per(bx), nty = (int32_t)per(by), ntz = (int32_t)per(bz);
+    const int32_t units = (int64_t)ntx * nty * ntz <= 256 ? kTileUnits : 1;
+    for (int32_t z = 0; z < ntz; ++z)
+      for (int32_t y = 0; y < nty; ++y)
+        for (int32_t x = 0; x < ntx; ++x) {
+          BrickTile t{};
+          t.rep = r;
+          t.cx = cut(nc, ntx, x);
+          t.cy = cut(nc, nty, y);
+          t.cz = cut(nc, ntz, z);
+          t.tx = cut(nc, ntx, x + 1) - t.cx;
+          t.ty = cut(nc, nty, y + 1) - t.cy;
+          t.tz = cut(nc, ntz, z + 1) - t.cz;
+          t.units = units;
+          t.part = c->brick_parts;
+          c->brick_parts += units;
+          const int32_t id = (int32_t)c->btiles_h.size();
+          c->btiles_h.push_back(t);
+          c->ba.rows = std::max(c->ba.rows, (t.ty + 2) * (t.tz + 2));
+          c->ba.hrows = std::max(c->ba.hrows, t.ty * t.tz);
+          c->brick_homes = std::max(c->brick_homes, ppc * t.tx * t.ty * t.tz);
+          auto n = [](int32_t t, int32_t h) { return (t + h - 1) / h; };
+          const int32_t ax = n(t.tx, hx), ay = n(t.ty, hy), az = n(t.tz, hz);
+          for (int32_t k = 0; k < ax * ay * az; ++k) {
+            const int32_t ix = k % ax, iy = k / ax % ay, iz = k / (ax * ay);
+            Brick b{};
+            b.tile = id;
+            b.lx = (int8_t)cut(t.tx, ax, ix);
+            b.ly = (int8_t)cut(t.ty, ay, iy);
+            b.lz = (int8_t)cut(t.tz, az, iz);
+            b.hx = (int8_t)(cut(t.tx, ax, ix + 1) - b.lx);
+            b.hy = (int8_t)(cut(t.ty, ay, iy + 1) - b.ly);
+            b.hz = (int8_t)(cut(t.tz, az, iz + 1) - b.lz);
+            c->bricks_h.push_back(b);
+          }
+        }
+    d.fb1 = c->brick_parts;
+  }
+  c->ba.ntiles = (int32_t)c->btiles_h.size();
+  c->ba.nbricks = (int32_t)c->bricks_h.size();
+  c->ba.slots = big ? kBrickSlotsBig : kBrickSlots;
+  c->ba.shift = big ? 2 : 3;
+  // few tiles: a tile's homes go to several blocks, each with a copy of the
+  // neighbourhood (4,000 particles, 27 tiles: a launch 16.4 us
+  // with one block per tile, 12.2 us with four; the gather kernel 17.2 us)
+  c->ba.split = c->ba.ntiles <= 64 ? 4 : (c->ba.ntiles <= 128 ? 2 : 1);
+  for (const BrickTile& t : c->btiles_h)
+    if (t.units == 1) c->ba.split = 1;
+  c->brick = true;
+  return true;
+}
+
 void drop_graph(md_ctx c);
 
 // Grow the neighbour capacity after an overflowed build to the longest row it
@@ -322,8 +522,31 @@ md_status grow_capacity(md_ctx c) {
   HIPCHECK(c, hipMemcpy(cnt.data(), c->ncount, sizeof(int32_t) * c->ntot, hipMemcpyDeviceToHost));
   int32_t m = 0;
   for (int32_t v : cnt) m = std::max(m, v);
+  if (c->brick) {
+    // chunks of rows built in several passes are not all full
+    std::vector<int32_t> ch(c->ntot);
+    HIPCHECK(c, hipMemcpy(ch.data(), c->ba.nchunk, sizeof(int32_t) * c->ntot,
+                          hipMemcpyDeviceToHost));
+    for (int32_t v : ch)
+      if (v > c->ba.capc) m = std::max(m, v * kChunkEntries);
+  }
   if (m <= c->cap) return fail(c, MD_EOVERFLOW, "overflow flagged with every row within capacity");
   const int32_t cap = std::max(c->cap, ((m + 16 + 7) / 8) * 8);
+  if (c->brick) {
+    uint4* fresh = nullptr;
+    const int32_t capc = cap / kChunkEntries + c->brick_extra;
+    md_status rc = dalloc(c, &fresh, chunk_elems(c->ntot, capc));
+    if (rc) return rc;
+    launch_relayout_chunks(c->stream, c->ntot, c->ba.nchunk, c->ba.capc, capc, c->ba.list, fresh);
+    HIPCHECK(c, hipGetLastError());
+    HIPCHECK(c, hipStreamSynchronize(c->stream));
+    dfree(c, c->ba.list);
+    c->ba.list = fresh;
+    c->ba.capc = capc;
+    c->cap = cap;
+    drop_graph(c);
+    return MD_OK;
+  }
   const int32_t elem = c->staged ? 2 : 4;
   void* old = c->staged ? (void*)c->nbr16 : (void*)c->nbr;
   md_status rc;
@@ -351,10 +574,56 @@ md_status grow_capacity(md_ctx c) {
   return MD_OK;
 }
 
+void plan_chunks(md_ctx c);
+
+// Partial-sum blocks of the gather path: tpp blocks per tile.
+void gather_blocks(md_ctx c) {
+  for (RepDesc& d : c->reps_h) {
+    d.fb0 = d.tile0 * c->tpp;
+    d.fb1 = d.tile1 * c->tpp;
+  }
+}
+
+md_status upload_blocks(md_ctx c) {
+  plan_chunks(c);
+  if (c->nchunks)
+    HIPCHECK(c, hipMemcpyAsync(c->chunks, c->chunks_h.data(), sizeof(RedChunk) * c->nchunks,
+                               hipMemcpyHostToDevice, c->stream));
+  HIPCHECK(c, hipMemcpyAsync(c->reps, c->reps_h.data(), sizeof(RepDesc) * c->nrep,
+                             hipMemcpyHostToDevice, c->stream));
+  // the host vectors are re-planned only after the copies finished
+  HIPCHECK(c, hipStreamSynchronize(c->stream));
+  return MD_OK;
+}
+
+// A tile whose neighbourhood outgrew the LDS slots (a box that condensed far
+// above its mean density): the context goes on with gather lists, which take
+// any density.  The caller rebuilds every replica.
+md_status leave_brick(md_ctx c) {
+  HIPCHECK(c, hipStreamSynchronize(c->stream));
+  dfree(c, c->ba.list);
+  c->ba.list = nullptr;
+  c->ba.ntiles = 0;
+  c->ba.nbricks = 0;
+  c->brick = false;
+  md_status rc = dalloc(c, &c->nbr, list_elems(c->ntot, c->cap));
+  if (!rc && c->mixed) rc = dalloc(c, &c->pos16, (size_t)c->stride);
+  if (!rc && c->mixed) rc = dalloc(c, &c->pos16_alt, (size_t)c->stride);
+  if (rc) {
+    c->built = false;
+    return rc;
+  }
+  c->tpp = 2;
+  c->unroll = 4;
+  gather_blocks(c);
+  drop_graph(c);
+  return upload_blocks(c);
+}
+
 // Full rebuild of every replica (md_build_cells and the first build after
 // md_set_state); grows the neighbour capacity once on overflow.
 md_status build_all(md_ctx c) {
-  for (int attempt = 0; attempt < 2; ++attempt) {
+  for (bool grown = false;;) {
     launch_mark_rebuild(c->stream, c->nrep, c->rebuild, c->st);
     run_chain(c, c->stream);
     launch_after_build(c->stream, c->nrep, c->rebuild, c->obs, c->st);
@@ -364,12 +633,17 @@ md_status build_all(md_ctx c) {
       c->forces_valid = false;
       return MD_OK;
     }
-    if (rc != MD_EOVERFLOW || attempt == 1) return rc;
-    if (c->err.find("LDS slots") != std::string::npos) return rc;  // not a capacity
-    rc = grow_capacity(c);
+    if (rc != MD_EOVERFLOW) return rc;
+    if (c->err.find("LDS slots") != std::string::npos) {  // not a capacity
+      if (!c->brick) return rc;
+      rc = leave_brick(c);
+    } else {
+      if (grown) return rc;
+      grown = true;
+      rc = grow_capacity(c);
+    }
     if (rc) return rc;
   }
-  return MD_OK;
 }
 
 ThermoArgs no_thermo() {
@@ -531,11 +805,11 @@ void drop_graph(md_ctx c) {
 // A graph of K steps, captured once per launch configuration and replayed:
 // every argument is fixed, the step number lives in device counters.
 md_status ensure_graph(md_ctx c, const ThermoArgs& ta, int32_t thermo, int32_t K) {
-  const int64_t key[15] = {K, thermo, ta.ramp, ta.log_every, ta.nlog, (int64_t)(intptr_t)ta.log,
+  const int64_t key[16] = {K, thermo, ta.ramp, ta.log_every, ta.nlog, (int64_t)(intptr_t)ta.log,
                            (int64_t)(intptr_t)c->nbr, (int64_t)(intptr_t)c->nbr16,
                            c->prof_every, c->prof_epoch, (int64_t)(intptr_t)c->pos,
-                           c->cap, c->lcap_f, c->tpp, c->unroll};
-  if (c->gexec && std::equal(key, key + 15, c->gkey)) return MD_OK;
+                           c->cap, c->lcap_f, c->tpp, c->unroll, (int64_t)(intptr_t)c->ba.list};
+  if (c->gexec && std::equal(key, key + 16, c->gkey)) return MD_OK;
   drop_graph(c);
   if (!c->cap_stream) HIPCHECK(c, hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
   md_status rc = reserve_events(c, K);
@@ -556,7 +830,7 @@ md_status ensure_graph(md_ctx c, const ThermoArgs& ta, int32_t thermo, int32_t K
     c->gexec = nullptr;
     return fail(c, MD_EHIP, "graph instantiation failed");
   }
-  std::copy(key, key + 15, c->gkey);
+  std::copy(key, key + 16, c->gkey);
   return MD_OK;
 }
 
@@ -738,11 +1012,15 @@ md_status md_init_alloc(md_ctx* out, const md_params* p, int32_t nrep, const int
     const int32_t room = lds_max - 8192;  // static LDS of the kernel
     c->lcap_f = std::max(64, std::min(want, (int32_t)(room / 24)));
     if (p->stage_slots > 0) c->lcap_f = std::min(c->lcap_f, p->stage_slots);
+  } else if (plan_bricks(c)) {
+    // lanes per particle: four fill the chip sooner (per NVE launch 32,000
+    // particles FP64 24 us against 33 with two, 131,072: 42 us both), two
+    // walk large boxes faster (1,048,576: 211 against 230 us, mixed 160
+    // against 190); results do not depend on it
+    c->tpp = ntot < 200000 ? 4 : 2;
+    c->unroll = kChunkEntries / c->tpp;
   } else {
-    for (RepDesc& d : c->reps_h) {
-      d.fb0 = d.tile0 * c->tpp;
-      d.fb1 = d.tile1 * c->tpp;
-    }
+    gather_blocks(c);
   }
   if (p->max_neighbors > 0) {
     c->cap = p->max_neighbors;
@@ -782,6 +1060,7 @@ md_status md_init_alloc(md_ctx* out, const md_params* p, int32_t nrep, const int
     tab.mass[a] = a < p->ntypes ? p->mass[a] : 1.0;
     tab.inv_mass[a] = 1.0 / tab.mass[a];
   }
+  if (c->brick) c->bp_h = brick_pair(*p, tab);
   c->thr_form = fma_pair_form(tab.thr, p->ntypes);
   c->rc2_form = fma_pair_form(tab.rc2, p->ntypes);
 
@@ -825,14 +1104,28 @@ md_status md_init_alloc(md_ctx* out, const md_params* p, int32_t nrep, const int
     ALLOC(f, 3 * S);
     c->frc = f;
   }
-  if (c->mixed && !c->staged && !c->cells) {
+  if (c->mixed && !c->brick && !c->staged && !c->cells) {
     ALLOC(c->pos16, S);
     ALLOC(c->pos16_alt, S);
   }
   ALLOC(c->id, N);
   ALLOC(c->id_tmp, N);
   ALLOC(c->img, 3 * N);
-  if (c->cells) {
+  if (c->brick) {
+    c->ba.capc = (c->cap + kChunkEntries - 1) / kChunkEntries + c->brick_extra;
+    BrickTile* bt = nullptr;
+    Brick* br = nullptr;
+    ALLOC(bt, (size_t)c->ba.ntiles);
+    ALLOC(br, (size_t)c->ba.nbricks);
+    c->ba.tiles = bt;
+    c->ba.bricks = br;
+    ALLOC(c->ba.head, (size_t)c->ba.ntiles);
+    ALLOC(c->ba.row, (size_t)c->ba.ntiles * c->ba.rows);
+    ALLOC(c->ba.hrow, (size_t)c->ba.ntiles * c->ba.hrows);
+    ALLOC(c->ba.list, chunk_elems(c->ntot, c->ba.capc));
+    ALLOC(c->ba.nchunk, N);
+    ALLOC(c->bp, 1);
+  } else if (c->cells) {
     ALLOC(c->rtiles, (size_t)c->nrt);
   } else if (c->staged) {
     ALLOC(c->nbr16, list_elems(c->ntot, c->cap));
@@ -842,13 +1135,13 @@ md_status md_init_alloc(md_ctx* out, const md_params* p, int32_t nrep, const int
     ALLOC(c->nbr, list_elems(c->ntot, c->cap));
   }
   if (!c->cells) ALLOC(c->ncount, N);  // list lengths (the list-free path has none)
-  ALLOC(c->part, 4 * std::max((size_t)c->ntiles * 8, (size_t)c->nrt));
+  const size_t most_blocks =
+      std::max({(size_t)c->ntiles * 8, (size_t)c->nrt, (size_t)c->brick_parts});
+  ALLOC(c->part, 4 * most_blocks);
   ALLOC(c->rebuild, (size_t)nrep);
   ALLOC(c->dmax, (size_t)c->ntiles);
   plan_chunks(c);
-  c->max_chunks =
-      (int32_t)((std::max((size_t)c->ntiles * 8, (size_t)c->nrt) + kRedChunk - 1) / kRedChunk) +
-      nrep;
+  c->max_chunks = (int32_t)((most_blocks + kRedChunk - 1) / kRedChunk) + nrep;
   ALLOC(c->chunks, (size_t)c->max_chunks);
   ALLOC(c->part2, (size_t)kPart2 * c->max_chunks);
   ALLOC(c->dpend, (size_t)nrep);
@@ -876,6 +1169,10 @@ md_status md_init_alloc(md_ctx* out, const md_params* p, int32_t nrep, const int
             up(c->tab, &tab, sizeof(PairTab)) &&
             up(c->cell_rep, cell_rep.data(), sizeof(int32_t) * c->ncells) &&
             up(c->lam, ones.data(), sizeof(double) * nrep) &&
+            (!c->brick ||
+             (up((void*)c->ba.tiles, c->btiles_h.data(), sizeof(BrickTile) * c->ba.ntiles) &&
+              up((void*)c->ba.bricks, c->bricks_h.data(), sizeof(Brick) * c->ba.nbricks) &&
+              up(c->bp, &c->bp_h, sizeof(BrickPair)))) &&
             (!(c->staged || c->cells) ||
              up(c->rtiles, c->rtiles_h.data(), sizeof(RowTile) * c->nrt)) &&
             (!c->nchunks || up(c->chunks, c->chunks_h.data(), sizeof(RedChunk) * c->nchunks)) &&
@@ -1042,10 +1339,19 @@ md_status md_step(md_ctx c, int32_t nsteps, const double* T0, const double* T1,
     HIPCHECK(c, hipStreamSynchronize(s));
     DevState st{};
     HIPCHECK(c, hipMemcpy(&st, c->st, sizeof(DevState), hipMemcpyDeviceToHost));
-    if (!(st.err & kErrOverflow) || (st.err & ~kErrOverflow) || attempt == 8) break;
+    const int32_t mend = kErrOverflow | (c->brick ? kErrSlots : 0);
+    if (!(st.err & mend) || (st.err & ~mend) || attempt == 8) break;
     int64_t done = 0;
     HIPCHECK(c, hipMemcpy(&done, c->kcall, sizeof(int64_t), hipMemcpyDeviceToHost));
-    rc = grow_capacity(c);
+    if (st.err & kErrSlots) {
+      rc = leave_brick(c);
+      if (!rc) {
+        launch_mark_rebuild(s, c->nrep, c->rebuild, c->st);
+        HIPCHECK(c, hipStreamSynchronize(s));
+      }
+    } else {
+      rc = grow_capacity(c);
+    }
     if (rc) {
       c->built = false;
       c->forces_valid = false;
@@ -1125,7 +1431,13 @@ md_status md_get_neighbors(md_ctx c, int32_t rep, int32_t* count, int32_t* ids, 
   if (cap > 0 && d.n > 0) {
     const uint32_t* src = c->nbr;
     uint32_t* tmp = nullptr;
-    if (c->staged) {
+    if (c->brick) {
+      md_status a_rc = dalloc(c, &tmp, list_elems(c->ntot, c->cap));
+      if (a_rc) return a_rc;
+      launch_decode_brick(c->stream, c->ba, c->cap, c->ncount, tmp);
+      HIPCHECK(c, hipStreamSynchronize(c->stream));
+      src = tmp;
+    } else if (c->staged) {
       // staged entries are LDS slots of the home tile: decode to particle indices
       md_status a_rc = dalloc(c, &tmp, list_elems(c->ntot, c->cap));
       if (a_rc) return a_rc;
@@ -1199,6 +1511,8 @@ md_status md_autotune(md_ctx c, int32_t reps, md_tune* out) {
   std::vector<std::pair<int32_t, int32_t>> cand;
   if (c->cells)
     cand = {{1, 1}};  // one kernel variant: nothing to choose
+  else if (c->brick)
+    cand = {{2, 4}, {4, 2}};  // lanes per particle, entries of a chunk per lane
   else if (c->staged)
     cand = {{1, 4}, {1, 8}, {2, 2}, {2, 4}, {2, 8}, {4, 2}};
   else
@@ -1236,20 +1550,11 @@ md_status md_autotune(md_ctx c, int32_t reps, md_tune* out) {
   (void)hipEventDestroy(e1);
   c->tpp = btpp;
   c->unroll = bun;
-  if (!c->staged && !c->cells) {
+  if (!c->brick && !c->staged && !c->cells) {
     // partial-sum blocks per replica follow the lanes per particle
-    for (RepDesc& d : c->reps_h) {
-      d.fb0 = d.tile0 * c->tpp;
-      d.fb1 = d.tile1 * c->tpp;
-    }
-    plan_chunks(c);
-    if (c->nchunks)
-      HIPCHECK(c, hipMemcpyAsync(c->chunks, c->chunks_h.data(), sizeof(RedChunk) * c->nchunks,
-                                 hipMemcpyHostToDevice, c->stream));
-    HIPCHECK(c, hipMemcpyAsync(c->reps, c->reps_h.data(), sizeof(RepDesc) * c->nrep,
-                               hipMemcpyHostToDevice, c->stream));
-    // the host vectors are re-planned only here, after the copies finished
-    HIPCHECK(c, hipStreamSynchronize(c->stream));
+    gather_blocks(c);
+    md_status rc = upload_blocks(c);
+    if (rc) return rc;
   }
   drop_graph(c);
   launch_forces0(c);

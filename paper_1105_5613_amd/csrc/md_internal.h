@@ -172,6 +172,9 @@ struct DevState {      // context scalars the kernels update
 };
 __device__ inline bool halted(const DevState* st) { return (st->err & kHalt) != 0; }
 
+struct BrickArgs;  // brick.h; ntiles = 0 off the brick path
+struct BrickPair;
+
 // ---- launchers (each file owns its kernels) ----------------------------------
 // cells.hip
 void launch_set_state(hipStream_t s, int32_t ntot, int32_t stride, const double* x,
@@ -187,6 +190,9 @@ void launch_mark_rebuild(hipStream_t s, int32_t nrep, int32_t* rebuild, DevState
 // or 4 bytes), when the capacity grows.
 void launch_relayout_list(hipStream_t s, int32_t ntot, const int32_t* ncount, int32_t cap_old,
                           int32_t cap_new, int32_t elem, const void* src, void* dst);
+// The same for the 16-byte chunks of the brick path (capacities in chunks).
+void launch_relayout_chunks(hipStream_t s, int32_t ntot, const int32_t* nchunk, int32_t cap_old,
+                            int32_t cap_new, const uint4* src, uint4* dst);
 void launch_zero_counts(hipStream_t s, int32_t ncells, const int32_t* cell_rep,
                         const int32_t* rebuild, const DevState* st, int32_t* counts);
 void launch_bin(hipStream_t s, int32_t ntiles, const Tile* tiles, const RepDesc* reps,
@@ -209,12 +215,13 @@ constexpr int kSmallCells = 4 * kSmallThreads;  // the scan takes four cells per
 void launch_chain_small(hipStream_t s, const RepDesc* reps, const int32_t* rebuild,
                         double4* pos, const int32_t* id, int32_t* img, int32_t* cell_start,
                         int32_t stride, const double* vel, int32_t* id_tmp, double4* pos_tmp,
-                        double* vel_tmp, DevState* st);
+                        double* vel_tmp, DevState* st, const BrickArgs& bricks);
 void launch_cell_gather(hipStream_t s, int32_t ncells, const int32_t* cell_rep,
                         const int32_t* rebuild, const int32_t* cell_start,
                         const int32_t* tmp_src, int32_t stride, const int32_t* id,
                         const double4* pos, const double* vel, int32_t* id_tmp,
-                        double4* pos_tmp, double* vel_tmp, const DevState* st);
+                        double4* pos_tmp, double* vel_tmp, DevState* st, const RepDesc* reps,
+                        const BrickArgs& bricks);
 // Form of a symmetric species-pair table t[a * 4 + b] (a, b < ntypes) in the
 // cut-off tests: 2 when every entry is t[0][b] + (t[1][b] - t[0][b]) * s_a
 // for the species value s_a in {0.0, 1.0} as one FMA, bit for bit -- one
@@ -276,6 +283,22 @@ void launch_force(hipStream_t s, int32_t mixed, int32_t mode, int32_t energy,
                   const PairTab* tab, const double4* pos, const int4* pos16, double* vel,
                   void* frc, const uint32_t* nbr, const int32_t* ncount, int32_t stride,
                   int32_t cap, double dt, double* part, DevState* st, const FuseOut& fo);
+// brick path (brick.h, nlist_brick.hip, force_brick.hip); modes and energy as
+// launch_force, threads per block a multiple of 64 up to kBrickThreads
+int32_t nlist_brick_pass();  // candidates per pass; each pass ends its rows' chunks
+void launch_nlist_brick(hipStream_t s, const BrickArgs& A, int32_t ntypes, const RepDesc* reps,
+                        const int32_t* rebuild, const PairTab* tab, const int32_t* cell_start,
+                        int32_t stride, int32_t cap, const BrickPair& bp,
+                        const double4* pos_tmp, const double* vel_tmp, const int32_t* id_tmp,
+                        double4* pos, double* vel, int32_t* id, double* xref, int32_t* ncount,
+                        DevState* st, int32_t spread);
+void launch_decode_brick(hipStream_t s, const BrickArgs& A, int32_t cap, const int32_t* ncount,
+                         uint32_t* out);
+void launch_force_brick(hipStream_t s, int32_t mixed, int32_t mode, int32_t energy, int32_t tpp,
+                        int32_t threads, int32_t four, const BrickArgs& A, const RepDesc* reps,
+                        const PairTab* tab, const BrickPair* bp, const double4* pos, double* vel,
+                        void* frc, int32_t stride, double dt, double* part, DevState* st,
+                        const FuseOut& fo);
 // integrate.hip
 void launch_kick_drift(hipStream_t s, int32_t mixed, int32_t thermo, int32_t ntiles,
                        const Tile* tiles, const RepDesc* reps, const PairTab* tab,
