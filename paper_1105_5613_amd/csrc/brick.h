@@ -50,7 +50,8 @@ struct Brick {
   int32_t tile;
   int8_t lx, ly, lz;    // first cell, relative to the tile's
   int8_t hx, hy, hz;    // cells per axis
-  int8_t pad[2];
+  int8_t pass;          // candidate chunks per pass of the list search
+  int8_t pad;
 };
 struct TileRow {        // row q = (y + 1) + (z + 1) (ty + 2) of the neighbourhood
   int32_t l0, l1, l2, l3;  // first slot of the left, main and right piece, end of the row

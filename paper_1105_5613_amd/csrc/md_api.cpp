@@ -437,7 +437,9 @@ bool plan_bricks(md_ctx c) {
           const int h = (x + 2) * (y + 2) * (z + 2), bh = (bx + 2) * (by + 2) * (bz + 2);
           if (v > bv || (v == bv && h < bh)) bx = x, by = y, bz = z;
         }
-    if (slots(ppc, bx, by, bz) >= kBrickSlots) big = true;
+    const bool rbig = slots(ppc, bx, by, bz) >= kBrickSlots;
+    const int32_t pass = nlist_brick_pass(rbig);
+    big |= rbig;
     // bricks of a tile: the matrix product takes 32 homes at a time against
     // 64 candidates; three chunks' worth of time per brick go elsewhere
     int hx = 1, hy = 1, hz = 1;
@@ -453,7 +455,7 @@ bool plan_bricks(md_ctx c) {
     const double cand = ppc * (hx + 2) * (hy + 2) * (hz + 2);
     c->ba.groups = std::max(c->ba.groups,
                             (int32_t)std::ceil(1.15 * ppc * hx * hy * hz / 32.0));
-    c->brick_extra = std::max(c->brick_extra, (int32_t)(1.15 * cand / nlist_brick_pass()));
+    c->brick_extra = std::max(c->brick_extra, (int32_t)(1.15 * cand / (64 * pass)));
     d.fb0 = c->brick_parts;
     auto cut = [](int32_t n, int32_t parts, int32_t k) {
       return (int32_t)((int64_t)n * k / parts);
@@ -485,6 +487,7 @@ bool plan_bricks(md_ctx c) {
             const int32_t ix = k % ax, iy = k / ax % ay, iz = k / (ax * ay);
             Brick b{};
             b.tile = id;
+            b.pass = (int8_t)pass;
             b.lx = (int8_t)cut(t.tx, ax, ix);
             b.ly = (int8_t)cut(t.ty, ay, iy);
             b.lz = (int8_t)cut(t.tz, az, iz);

@@ -285,7 +285,9 @@ void launch_force(hipStream_t s, int32_t mixed, int32_t mode, int32_t energy,
                   int32_t cap, double dt, double* part, DevState* st, const FuseOut& fo);
 // brick path (brick.h, nlist_brick.hip, force_brick.hip); modes and energy as
 // launch_force, threads per block a multiple of 64 up to kBrickThreads
-int32_t nlist_brick_pass();  // candidates per pass; each pass ends its rows' chunks
+// candidate chunks (of 64) per pass of a replica whose tiles need the larger
+// LDS layout or not; each pass ends its rows' chunks
+int32_t nlist_brick_pass(bool big);
 void launch_nlist_brick(hipStream_t s, const BrickArgs& A, int32_t ntypes, const RepDesc* reps,
                         const int32_t* rebuild, const PairTab* tab, const int32_t* cell_start,
                         int32_t stride, int32_t cap, const BrickPair& bp,

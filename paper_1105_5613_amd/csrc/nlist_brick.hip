@@ -31,8 +31,8 @@
 // the first candidate on and one from the last back, and pack eight entries
 // to a 16-byte chunk in registers, stored whole.  The order of a row is not
 // specified; it is the same in every launch.  Places of the last chunk past
-// the row's end point at the far slot (a pass of more than kNbChunks * 64
-// candidates ends its rows' chunks like that too).
+// the row's end point at the far slot (a search of several passes
+// ends each pass like that).
 //
 // Measured at 1,048,576 particles (LJ box, list radius 2.8): 290 us; the VALU
 // search of nlist.hip writing 32-bit entries takes 550 us.
@@ -46,7 +46,11 @@ namespace mdk {
 namespace {
 
 constexpr int kNbGroup = 32;    // home particles per group (columns of the product)
-constexpr int kNbChunks = 12;   // candidate chunks per pass
+// Candidate chunks per pass.  A 1 x 1 x 1 brick of cells 2.8 to 3 wide
+// (replicas that need the larger LDS layout) has up to 14 chunks of
+// candidates: with 12 it took two passes (64 replicas of 1,000 to 65,536, a
+// fifth rebuilding: 167 us per launch, 158 with 15).
+constexpr int kNbChunks = 12, kNbChunksBig = 15;
 constexpr int kNbWaves = 4;     // bricks per block
 constexpr int kCoopWaves = 8;   // waves per brick (COOP)
 constexpr int kCoopBlocks = 1024;  // most blocks of the COOP form
@@ -112,9 +116,9 @@ __device__ inline double image(uint32_t code, int lsb) {
 // sixteenth list chunk of a home in the write phase, starting at that chunk's
 // rank; a brick's groups of homes go to `groups` blocks.  The rows are the
 // same, entry for entry.  15 us in that box (nlist_small.hip: 28 us).
-template <int NS, bool COOP>
+template <int NS, bool COOP, int CH>
 __global__ __launch_bounds__(64 * (COOP ? kCoopWaves : kNbWaves))
-__attribute__((amdgpu_waves_per_eu(COOP ? 4 : 5))) void
+__attribute__((amdgpu_waves_per_eu(COOP || CH > kNbChunks ? 4 : 5))) void
 k_nlist_brick(BrickArgs A, const RepDesc* __restrict__ reps, const int32_t* __restrict__ rebuild,
               const PairTab* __restrict__ tab, const int32_t* __restrict__ cell_start,
               int32_t stride, int32_t cap, int32_t flip, const double4* __restrict__ pos_tmp,
@@ -127,10 +131,10 @@ k_nlist_brick(BrickArgs A, const RepDesc* __restrict__ reps, const int32_t* __re
   constexpr int kShare = COOP ? kCoopWaves : 1;     // waves per brick
   __shared__ double s_thr[16];
   __shared__ uint32_t s_n[COOP ? kW : 1][64], s_full[COOP ? kW : 1][64];
-  __shared__ uint32_t s_kc[kB][kNbChunks * 64];  // sorted index | image code
-  __shared__ uint16_t s_ent[kB][kNbChunks * 64];  // list entry
+  __shared__ uint32_t s_kc[kB][CH * 64];  // sorted index | image code
+  __shared__ uint16_t s_ent[kB][CH * 64];  // list entry
   // [word][home], a spare row before and after a wave's
-  __shared__ uint32_t s_hits[kB][(2 * kNbChunks + 2) * kNbGroup];
+  __shared__ uint32_t s_hits[kB][(2 * CH + 2) * kNbGroup];
   if (!st->any_rebuild) return;  // whole block: one flag load when nothing rebuilds
   if (threadIdx.x < 16) s_thr[threadIdx.x] = tab->thr[threadIdx.x];
   __syncthreads();
@@ -233,6 +237,8 @@ k_nlist_brick(BrickArgs A, const RepDesc* __restrict__ reps, const int32_t* __re
   // groups of at most kNbGroup home particles, of equal size
   const int32_t ngrp = (nh + kNbGroup - 1) / kNbGroup;
   const int32_t gsz = ngrp ? (nh + ngrp - 1) / ngrp : 1;
+  // (the replica's own, not the context's: the order of its rows depends on it)
+  const int32_t pass = 64 * (CH > kNbChunks ? min((int32_t)B.pass, CH) : CH);
   int32_t filled = -1;  // the pass whose candidates kc and ent hold
   for (int32_t g0 = grp * gsz; g0 < nh; g0 += gsz * (COOP ? groups : 1)) {
     const int32_t gn = nh - g0 < gsz ? nh - g0 : gsz;
@@ -254,8 +260,8 @@ k_nlist_brick(BrickArgs A, const RepDesc* __restrict__ reps, const int32_t* __re
       b2 = seg ? (hl < gn ? uu - a0 : no_hit) : -d1;
       if constexpr (NS > 2) b3 = (float)(th[0] - th[seg ? 3 : 2]);
     }
-    for (int32_t pb = 0; pb < ncand; pb += kNbChunks * 64) {
-      const int32_t np = ncand - pb < kNbChunks * 64 ? ncand - pb : kNbChunks * 64;
+    for (int32_t pb = 0; pb < ncand; pb += pass) {
+      const int32_t np = ncand - pb < pass ? ncand - pb : pass;
       const int32_t nwords = 2 * ((np + 63) >> 6);
       if (filled != pb) {
         // index, image and slot of every candidate of the pass
@@ -549,7 +555,7 @@ __global__ __launch_bounds__(256) void k_decode_brick(BrickArgs A, int32_t cap,
 
 }  // namespace
 
-int32_t nlist_brick_pass() { return kNbChunks * 64; }
+int32_t nlist_brick_pass(bool big) { return big ? kNbChunksBig : kNbChunks; }
 
 void launch_nlist_brick(hipStream_t s, const BrickArgs& A, int32_t ntypes, const RepDesc* reps,
                         const int32_t* rebuild, const PairTab* tab, const int32_t* cell_start,
@@ -561,17 +567,22 @@ void launch_nlist_brick(hipStream_t s, const BrickArgs& A, int32_t ntypes, const
   const int32_t g = spread / kNbWaves, grid = g ? spread_grid(nb, g) : nb;
   // entries carry the species as one bit (two-species constants) or as two
   // (the table of up to four)
-#define KB(NS, CO, GRID, W)                                                                     \
-  k_nlist_brick<NS, CO><<<GRID, 64 * W, 0, s>>>(A, reps, rebuild, tab, cell_start, stride, cap, \
-                                                bp.flip, pos_tmp, vel_tmp, id_tmp, pos, vel, id, \
-                                                xref, ncount, st, g, A.groups)
+#define KB(NS, CO, CH, GRID, W)                                                          \
+  k_nlist_brick<NS, CO, CH><<<GRID, 64 * W, 0, s>>>(                                     \
+      A, reps, rebuild, tab, cell_start, stride, cap, bp.flip, pos_tmp, vel_tmp, id_tmp, \
+      pos, vel, id, xref, ncount, st, g, A.groups)
+#define KC(NS, CH)                                                          \
+  if (A.nbricks * A.groups <= kCoopBlocks)                                  \
+    KB(NS, true, CH, A.nbricks * A.groups, kCoopWaves);                     \
+  else                                                                      \
+    KB(NS, false, CH, grid, kNbWaves)
   const bool four = bp.four || ntypes > 2;
-  if (A.nbricks * A.groups <= kCoopBlocks) {
-    if (four) KB(4, true, A.nbricks * A.groups, kCoopWaves);
-    else KB(2, true, A.nbricks * A.groups, kCoopWaves);
+  if (A.slots > kBrickSlots) {
+    if (four) { KC(4, kNbChunksBig); } else { KC(2, kNbChunksBig); }
   } else {
-    if (four) KB(4, false, grid, kNbWaves); else KB(2, false, grid, kNbWaves);
+    if (four) { KC(4, kNbChunks); } else { KC(2, kNbChunks); }
   }
+#undef KC
 #undef KB
 }
 
