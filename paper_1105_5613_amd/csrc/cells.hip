@@ -166,38 +166,43 @@ __global__ __launch_bounds__(kTile) void k_bin(const Tile* __restrict__ tiles,
                                                int32_t* __restrict__ counts,
                                                int32_t* __restrict__ cell_of,
                                                int32_t* __restrict__ slot, DevState* st,
-                                               int32_t ntiles, int32_t spread) {
+                                               int32_t ntiles, int32_t spread,
+                                               int32_t nblk) {
   if (!st->any_rebuild) return;  // one flag load when nothing rebuilds
-  const int32_t lt = spread ? xcd_spread(blockIdx.x, spread) : xcd_block(blockIdx.x, gridDim.x);
-  if (lt >= ntiles) return;
-  const Tile t = tiles[lt];
-  if (!rebuild[t.rep]) return;
-  const int lane = threadIdx.x & 63;
-  const int32_t i = t.start + threadIdx.x;
-  const int32_t wave0 = t.start + (int32_t)(threadIdx.x & ~63u);
-  if (wave0 >= t.end) return;  // whole wave past the tile
-  const bool active = i < t.end;
-  const RepDesc R = reps[t.rep];
-  int32_t c = -1;
-  if (active) {
-    double4 p = pos[i];
-    c = bin_particle(i, p, R, pos, id, img, st);
-    cell_of[i] = c;
+  auto tile = [&](int32_t lt) {
+    const Tile t = tiles[lt];
+    if (!rebuild[t.rep]) return;
+    const int lane = threadIdx.x & 63;
+    const int32_t i = t.start + threadIdx.x;
+    const int32_t wave0 = t.start + (int32_t)(threadIdx.x & ~63u);
+    if (wave0 >= t.end) return;  // whole wave past the tile
+    const bool active = i < t.end;
+    const RepDesc R = reps[t.rep];
+    int32_t c = -1;
+    if (active) {
+      double4 p = pos[i];
+      c = bin_particle(i, p, R, pos, id, img, st);
+      cell_of[i] = c;
+    }
+    // runs of equal cell among consecutive active lanes
+    const int32_t cp = __shfl_up(c, 1, 64);
+    const bool lead = active && (lane == 0 || cp != c);
+    const uint64_t leaders = __ballot(lead);
+    const uint64_t act = __ballot(active);
+    const uint64_t upto = lane == 63 ? ~0ull : ((2ull << lane) - 1ull);
+    const int my_lead = 63 - __builtin_clzll((leaders & upto) | 1ull);
+    const uint64_t after = my_lead == 63 ? 0ull : (leaders >> (my_lead + 1));
+    const int n_act = __popcll(act);
+    const int next = after ? my_lead + 1 + __builtin_ctzll(after) : n_act;
+    int32_t base = 0;
+    if (lead) base = atomicAdd(&counts[c], next - my_lead);
+    base = __shfl(base, my_lead, 64);
+    if (active) slot[i] = base + (lane - my_lead);
+  };
+  for (int32_t b = blockIdx.x; b < nblk; b += gridDim.x) {
+    const int32_t lt = spread ? xcd_spread(b, spread) : xcd_block(b, nblk);
+    if (lt < ntiles) tile(lt);
   }
-  // runs of equal cell among consecutive active lanes
-  const int32_t cp = __shfl_up(c, 1, 64);
-  const bool lead = active && (lane == 0 || cp != c);
-  const uint64_t leaders = __ballot(lead);
-  const uint64_t act = __ballot(active);
-  const uint64_t upto = lane == 63 ? ~0ull : ((2ull << lane) - 1ull);
-  const int my_lead = 63 - __builtin_clzll((leaders & upto) | 1ull);
-  const uint64_t after = my_lead == 63 ? 0ull : (leaders >> (my_lead + 1));
-  const int n_act = __popcll(act);
-  const int next = after ? my_lead + 1 + __builtin_ctzll(after) : n_act;
-  int32_t base = 0;
-  if (lead) base = atomicAdd(&counts[c], next - my_lead);
-  base = __shfl(base, my_lead, 64);
-  if (active) slot[i] = base + (lane - my_lead);
 }
 
 // ---- exclusive scan of the cell counts ------------------------------------------
@@ -366,15 +371,18 @@ __global__ __launch_bounds__(kTile) void k_scatter(const Tile* __restrict__ tile
                                                    const int32_t* __restrict__ cell_start,
                                                    int32_t* __restrict__ tmp_src,
                                                    const DevState* __restrict__ st,
-                                                   int32_t ntiles, int32_t spread) {
+                                                   int32_t ntiles, int32_t spread,
+                                                   int32_t nblk) {
   if (!st->any_rebuild) return;
-  const int32_t lt = spread ? xcd_spread(blockIdx.x, spread) : xcd_block(blockIdx.x, gridDim.x);
-  if (lt >= ntiles) return;
-  const Tile t = tiles[lt];
-  if (!rebuild[t.rep]) return;
-  const int32_t i = t.start + threadIdx.x;
-  if (i >= t.end) return;
-  tmp_src[cell_start[cell_of[i]] + slot[i]] = i;
+  for (int32_t b = blockIdx.x; b < nblk; b += gridDim.x) {
+    const int32_t lt = spread ? xcd_spread(b, spread) : xcd_block(b, nblk);
+    if (lt >= ntiles) continue;
+    const Tile t = tiles[lt];
+    if (!rebuild[t.rep]) continue;
+    const int32_t i = t.start + threadIdx.x;
+    if (i >= t.end) continue;
+    tmp_src[cell_start[cell_of[i]] + slot[i]] = i;
+  }
 }
 
 // One wave per cell: rank the cell's particles by original id (ids are
@@ -386,56 +394,59 @@ __global__ __launch_bounds__(256) void k_cell_gather(
     const int32_t* __restrict__ id, const double4* __restrict__ pos,
     const double* __restrict__ vel, int32_t* __restrict__ id_tmp, double4* __restrict__ pos_tmp,
     double* __restrict__ vel_tmp, DevState* st, int32_t nbc, const RepDesc* __restrict__ reps,
-    BrickArgs A) {
+    BrickArgs A, int32_t nblk) {
   if (!st->any_rebuild) return;
   const int lane = threadIdx.x & 63;
-  if ((int32_t)blockIdx.x >= nbc) {
-    const int32_t t = ((int32_t)blockIdx.x - nbc) * 4 + (threadIdx.x >> 6);
-    if (t >= A.ntiles) return;
-    const BrickTile T = A.tiles[t];
-    if (rebuild[T.rep])
-      tile_rows(T, reps[T.rep], cell_start, lane, A.slots, A.head + t, A.row + (size_t)t * A.rows,
-                A.hrow + (size_t)t * A.hrows, st);
-    return;
-  }
-  const int32_t c = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (c >= ncells) return;
-  if (!rebuild[cell_rep[c]]) return;
-  const int32_t s = cell_start[c], n = cell_start[c + 1] - s;
-  if (n <= 64) {
-    int32_t src = 0, myid = 0x7fffffff;
-    if (lane < n) {
-      src = tmp_src[s + lane];
-      myid = id[src];
+  auto block = [&](int32_t b) {
+    if (b >= nbc) {
+      const int32_t t = (b - nbc) * 4 + (threadIdx.x >> 6);
+      if (t >= A.ntiles) return;
+      const BrickTile T = A.tiles[t];
+      if (rebuild[T.rep])
+        tile_rows(T, reps[T.rep], cell_start, lane, A.slots, A.head + t, A.row + (size_t)t * A.rows,
+                  A.hrow + (size_t)t * A.hrows, st);
+      return;
     }
-    int32_t rank = 0;
-    for (int m = 0; m < n; ++m) {
-      int32_t o = __shfl(myid, m, 64);
-      rank += (o < myid) ? 1 : 0;
-    }
-    if (lane < n) {
-      int32_t d = s + rank;
-      id_tmp[d] = myid;
-      pos_tmp[d] = pos[src];
-      vel_tmp[d] = vel[src];
-      vel_tmp[stride + d] = vel[stride + src];
-      vel_tmp[2 * (size_t)stride + d] = vel[2 * (size_t)stride + src];
-    }
-  } else {
-    // crowded cell: quadratic rank straight from memory
-    for (int32_t k = lane; k < n; k += 64) {
-      int32_t src = tmp_src[s + k];
-      int32_t myid = id[src];
+    const int32_t c = b * 4 + (threadIdx.x >> 6);
+    if (c >= ncells) return;
+    if (!rebuild[cell_rep[c]]) return;
+    const int32_t s = cell_start[c], n = cell_start[c + 1] - s;
+    if (n <= 64) {
+      int32_t src = 0, myid = 0x7fffffff;
+      if (lane < n) {
+        src = tmp_src[s + lane];
+        myid = id[src];
+      }
       int32_t rank = 0;
-      for (int32_t m = 0; m < n; ++m) rank += (id[tmp_src[s + m]] < myid) ? 1 : 0;
-      int32_t d = s + rank;
-      id_tmp[d] = myid;
-      pos_tmp[d] = pos[src];
-      vel_tmp[d] = vel[src];
-      vel_tmp[stride + d] = vel[stride + src];
-      vel_tmp[2 * (size_t)stride + d] = vel[2 * (size_t)stride + src];
+      for (int m = 0; m < n; ++m) {
+        int32_t o = __shfl(myid, m, 64);
+        rank += (o < myid) ? 1 : 0;
+      }
+      if (lane < n) {
+        int32_t d = s + rank;
+        id_tmp[d] = myid;
+        pos_tmp[d] = pos[src];
+        vel_tmp[d] = vel[src];
+        vel_tmp[stride + d] = vel[stride + src];
+        vel_tmp[2 * (size_t)stride + d] = vel[2 * (size_t)stride + src];
+      }
+    } else {
+      // crowded cell: quadratic rank straight from memory
+      for (int32_t k = lane; k < n; k += 64) {
+        int32_t src = tmp_src[s + k];
+        int32_t myid = id[src];
+        int32_t rank = 0;
+        for (int32_t m = 0; m < n; ++m) rank += (id[tmp_src[s + m]] < myid) ? 1 : 0;
+        int32_t d = s + rank;
+        id_tmp[d] = myid;
+        pos_tmp[d] = pos[src];
+        vel_tmp[d] = vel[src];
+        vel_tmp[stride + d] = vel[stride + src];
+        vel_tmp[2 * (size_t)stride + d] = vel[2 * (size_t)stride + src];
+      }
     }
-  }
+  };
+  for (int32_t b = blockIdx.x; b < nblk; b += gridDim.x) block(b);
 }
 
 // The whole chain for a context of one replica with at most kSmallN
@@ -612,8 +623,8 @@ void launch_bin(hipStream_t s, int32_t ntiles, const Tile* tiles, const RepDesc*
                 const int32_t* rebuild, double4* pos, const int32_t* id, int32_t* img,
                 int32_t* counts, int32_t* cell_of, int32_t* slot, DevState* st, int32_t spread) {
   const int32_t grid = spread ? spread_grid(ntiles, spread) : ntiles;
-  k_bin<<<grid, kTile, 0, s>>>(tiles, reps, rebuild, pos, id, img, counts, cell_of, slot, st,
-                               ntiles, spread);
+  k_bin<<<gated_grid(grid, spread != 0), kTile, 0, s>>>(tiles, reps, rebuild, pos, id, img, counts, cell_of, slot, st,
+                               ntiles, spread, grid);
 }
 
 size_t scan_bsum_elems(int32_t ncells) { return (size_t)nblk(ncells, kScanBlock) + 1; }
@@ -634,8 +645,8 @@ void launch_scatter(hipStream_t s, int32_t ntiles, const Tile* tiles, const int3
                     const int32_t* cell_of, const int32_t* slot, const int32_t* cell_start,
                     int32_t* tmp_src, const DevState* st, int32_t spread) {
   const int32_t grid = spread ? spread_grid(ntiles, spread) : ntiles;
-  k_scatter<<<grid, kTile, 0, s>>>(tiles, rebuild, cell_of, slot, cell_start, tmp_src, st,
-                                   ntiles, spread);
+  k_scatter<<<gated_grid(grid, spread != 0), kTile, 0, s>>>(tiles, rebuild, cell_of, slot, cell_start, tmp_src, st,
+                                   ntiles, spread, grid);
 }
 
 void launch_chain_small(hipStream_t s, const RepDesc* reps, const int32_t* rebuild,
@@ -651,11 +662,12 @@ void launch_cell_gather(hipStream_t s, int32_t ncells, const int32_t* cell_rep,
                         const int32_t* tmp_src, int32_t stride, const int32_t* id,
                         const double4* pos, const double* vel, int32_t* id_tmp,
                         double4* pos_tmp, double* vel_tmp, DevState* st, const RepDesc* reps,
-                        const BrickArgs& bricks) {
+                        const BrickArgs& bricks, bool several) {
   const int32_t nbc = (int32_t)nblk(ncells, 4);
-  k_cell_gather<<<nbc + nblk(bricks.ntiles, 4), 256, 0, s>>>(
+  const int32_t nb = nbc + (int32_t)nblk(bricks.ntiles, 4);
+  k_cell_gather<<<gated_grid(nb, several), 256, 0, s>>>(
       ncells, cell_rep, rebuild, cell_start, tmp_src, stride, id, pos, vel, id_tmp, pos_tmp,
-      vel_tmp, st, nbc, reps, bricks);
+      vel_tmp, st, nbc, reps, bricks, nb);
 }
 
 }  // namespace mdk

@@ -266,24 +266,26 @@ __global__ __launch_bounds__(kCellHomes) __attribute__((amdgpu_waves_per_eu(6)))
 // reference positions of the skin rule are reset (the list-building kernels
 // do this on the other paths).
 __global__ __launch_bounds__(kTile) void k_commit_order(
-    const Tile* __restrict__ tiles, const int32_t* __restrict__ rebuild, int32_t stride,
+    int32_t ntiles, const Tile* __restrict__ tiles, const int32_t* __restrict__ rebuild, int32_t stride,
     const double4* __restrict__ pos_tmp, const double* __restrict__ vel_tmp,
     const int32_t* __restrict__ id_tmp, double4* __restrict__ pos, double* __restrict__ vel,
     int32_t* __restrict__ id, double* __restrict__ xref, const DevState* __restrict__ st) {
   if (!st->any_rebuild) return;
-  const Tile t = tiles[xcd_block(blockIdx.x, gridDim.x)];
-  if (!rebuild[t.rep]) return;
-  const int32_t i = t.start + threadIdx.x;
-  if (i >= t.end) return;
-  const double4 p = pos_tmp[i];
-  pos[i] = p;
-  xref[i] = p.x;
-  xref[stride + i] = p.y;
-  xref[2 * (size_t)stride + i] = p.z;
-  vel[i] = vel_tmp[i];
-  vel[stride + i] = vel_tmp[stride + i];
-  vel[2 * (size_t)stride + i] = vel_tmp[2 * (size_t)stride + i];
-  id[i] = id_tmp[i];
+  for (int32_t b = blockIdx.x; b < ntiles; b += gridDim.x) {
+    const Tile t = tiles[xcd_block(b, ntiles)];
+    if (!rebuild[t.rep]) continue;
+    const int32_t i = t.start + threadIdx.x;
+    if (i >= t.end) continue;
+    const double4 p = pos_tmp[i];
+    pos[i] = p;
+    xref[i] = p.x;
+    xref[stride + i] = p.y;
+    xref[2 * (size_t)stride + i] = p.z;
+    vel[i] = vel_tmp[i];
+    vel[stride + i] = vel_tmp[stride + i];
+    vel[2 * (size_t)stride + i] = vel_tmp[2 * (size_t)stride + i];
+    id[i] = id_tmp[i];
+  }
 }
 
 }  // namespace
@@ -313,7 +315,7 @@ void launch_commit_order(hipStream_t s, int32_t ntiles, const Tile* tiles,
                          const int32_t* rebuild, int32_t stride, const double4* pos_tmp,
                          const double* vel_tmp, const int32_t* id_tmp, double4* pos,
                          double* vel, int32_t* id, double* xref, const DevState* st) {
-  k_commit_order<<<ntiles, kTile, 0, s>>>(tiles, rebuild, stride, pos_tmp, vel_tmp, id_tmp, pos,
+  k_commit_order<<<gated_grid(ntiles, false), kTile, 0, s>>>(ntiles, tiles, rebuild, stride, pos_tmp, vel_tmp, id_tmp, pos,
                                           vel, id, xref, st);
 }
 

@@ -280,7 +280,7 @@ void run_chain(md_ctx c, hipStream_t s, bool zeroed = false) {
                    c->tmp_src, c->st, spread_t);
     launch_cell_gather(s, c->ncells, c->cell_rep, c->rebuild, c->cell_start, c->tmp_src,
                        c->stride, c->id, c->pos, c->vel, c->id_tmp, c->pos_tmp, c->vel_tmp,
-                       c->st, c->reps, c->ba);
+                       c->st, c->reps, c->ba, c->nrep > 1);
   }
   if (c->brick)
     launch_nlist_brick(s, c->ba, c->p.ntypes, c->reps, c->rebuild, c->tab, c->cell_start,

@@ -155,6 +155,21 @@ inline int32_t spread_grid(int32_t nb, int32_t g) {
   return (nb + m - 1) / m * m;
 }
 
+// Grid of a kernel of the rebuild chain: at most kGatedGrid blocks, which
+// loop over the logical ones.  A chain launch of a step that rebuilds nothing
+// reads one flag and ends; past some thousand blocks it costs 0.2 us per
+// thousand (the 1M-particle soft-sphere box, 65,536 blocks: 14 us each for
+// the gather and the list search, of 155 us per step).  A multiple of kXcd,
+// so that a block's logical ones share its XCD (xcd_block).  With several
+// replicas nearly every step rebuilds some and the grid stays whole; so does
+// the brick search's, which has four bricks to a block (its loop cost 1 to 2 %
+// of a batch's step in scalar spills, and gained nothing at 16,777,216
+// particles).
+constexpr int32_t kGatedGrid = 8192;
+inline int32_t gated_grid(int32_t nb, bool several) {
+  return several || nb < kGatedGrid ? nb : kGatedGrid;
+}
+
 // The force kernel reads the list with non-temporal loads when one replica's
 // list (capacity) exceeds this: about 1.5x the 256 MB last-level (Infinity)
 // cache, a list that would not stay cached between launches anyway.  Smaller
@@ -221,7 +236,7 @@ void launch_cell_gather(hipStream_t s, int32_t ncells, const int32_t* cell_rep,
                         const int32_t* tmp_src, int32_t stride, const int32_t* id,
                         const double4* pos, const double* vel, int32_t* id_tmp,
                         double4* pos_tmp, double* vel_tmp, DevState* st, const RepDesc* reps,
-                        const BrickArgs& bricks);
+                        const BrickArgs& bricks, bool several);
 // Form of a symmetric species-pair table t[a * 4 + b] (a, b < ntypes) in the
 // cut-off tests: 2 when every entry is t[0][b] + (t[1][b] - t[0][b]) * s_a
 // for the species value s_a in {0.0, 1.0} as one FMA, bit for bit -- one

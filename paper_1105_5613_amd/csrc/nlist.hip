@@ -238,7 +238,7 @@ __global__ __launch_bounds__(64 * kCwWaves) void k_nlist_cells(
     typename std::conditional<TILE, uint16_t, uint32_t>::type* __restrict__ nbr,
     int32_t* __restrict__ ncount, DevState* st, int4* __restrict__ pos16,
     const int32_t* __restrict__ cell_tile, const RowTile* __restrict__ rtiles, int32_t dcode,
-    int32_t spread) {
+    int32_t spread, int32_t nblk) {
   using E = typename std::conditional<TILE, uint16_t, uint32_t>::type;
   __shared__ double s_thr[16];
   __shared__ int32_t s_pre[kCwWaves][28];    // first packed candidate of piece p
@@ -256,315 +256,319 @@ __global__ __launch_bounds__(64 * kCwWaves) void k_nlist_cells(
   __syncthreads();
   // the wave index is wave-uniform; as a scalar, the per-cell values below are too
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int32_t c =
-      (spread ? xcd_spread(blockIdx.x, spread) : xcd_block(blockIdx.x, gridDim.x)) * kCwWaves + w;
-  if (c >= ncells) return;
-  const int32_t r = cell_rep[c];
-  if (!rebuild[r]) return;
-  const RepDesc R = reps[r];
-  if (R.nc == 1) return;  // minimum-image kernel
-  const int32_t nc = R.nc;
-  const int32_t lc = c - R.coff;
-  const int32_t qx = lc % nc, qy = (lc / nc) % nc, qz = lc / (nc * nc);
-  const int32_t h0 = cell_start[c], nh = cell_start[c + 1] - h0;
-  uint32_t* const ent = s_ent[w];
-  uint32_t* const hits = s_hits[w];
+  auto cell = [&](int32_t c) {
+    const int32_t r = cell_rep[c];
+    if (!rebuild[r]) return;
+    const RepDesc R = reps[r];
+    if (R.nc == 1) return;  // minimum-image kernel
+    const int32_t nc = R.nc;
+    const int32_t lc = c - R.coff;
+    const int32_t qx = lc % nc, qy = (lc / nc) % nc, qz = lc / (nc * nc);
+    const int32_t h0 = cell_start[c], nh = cell_start[c + 1] - h0;
+    uint32_t* const ent = s_ent[w];
+    uint32_t* const hits = s_hits[w];
 
-  int32_t own_slot = 13;  // piece holding the home cell's particles
-  if constexpr (!TILE) {
-    // gather path: the 27 cells as single-cell pieces, the home cell first,
-    // then each forward offset o (in (dz, dy, dx) order) followed by its
-    // mirror -o; lane q < 27 builds offset q.  A particle's place in its
-    // cell moves hits between o and -o but hardly changes their sum, so
-    // after every pair the particles of a wave have used about the same
-    // number of entries, and the force kernel's gathers at one entry index
-    // fall in the same cells more often than with rows in (dz, dy, dx) order.
-    if (lane < 27) {
-      const int32_t ox = lane % 3 - 1, oy = (lane / 3) % 3 - 1, oz = lane / 9 - 1;
-      int32_t nx, sx, ny, sy, nz, sz;
-      stencil_axis(qx, ox, nc, nx, sx);
-      stencil_axis(qy, oy, nc, ny, sy);
-      stencil_axis(qz, oz, nc, nz, sz);
-      const int32_t cn = R.coff + (nz * nc + ny) * nc + nx;
-      const int32_t slot = lane == 13 ? 0 : (lane > 13 ? 2 * (lane - 13) - 1 : 2 * (13 - lane));
-      s_k0[w][slot] = cell_start[cn];
-      s_pre[w][slot] = cell_start[cn + 1] - cell_start[cn];  // lengths for now
-      const uint32_t code = image_code(sx, sy, sz);
-      s_code[w][slot] = (int32_t)code;
-      // mixed lists: d = c_i - c_j - s nc = -o
-      s_ecode[w][slot] = (int32_t)(dcode ? image_code(-ox, -oy, -oz) : code);
-    }
-    own_slot = 0;
-    wave_lds_sync();
-    if (lane == 0) {
-      int32_t acc = 0;
-      for (int p = 0; p < 27; ++p) {
-        const int32_t len = s_pre[w][p];
-        s_pre[w][p] = acc;
-        acc += len;
+    int32_t own_slot = 13;  // piece holding the home cell's particles
+    if constexpr (!TILE) {
+      // gather path: the 27 cells as single-cell pieces, the home cell first,
+      // then each forward offset o (in (dz, dy, dx) order) followed by its
+      // mirror -o; lane q < 27 builds offset q.  A particle's place in its
+      // cell moves hits between o and -o but hardly changes their sum, so
+      // after every pair the particles of a wave have used about the same
+      // number of entries, and the force kernel's gathers at one entry index
+      // fall in the same cells more often than with rows in (dz, dy, dx) order.
+      if (lane < 27) {
+        const int32_t ox = lane % 3 - 1, oy = (lane / 3) % 3 - 1, oz = lane / 9 - 1;
+        int32_t nx, sx, ny, sy, nz, sz;
+        stencil_axis(qx, ox, nc, nx, sx);
+        stencil_axis(qy, oy, nc, ny, sy);
+        stencil_axis(qz, oz, nc, nz, sz);
+        const int32_t cn = R.coff + (nz * nc + ny) * nc + nx;
+        const int32_t slot = lane == 13 ? 0 : (lane > 13 ? 2 * (lane - 13) - 1 : 2 * (13 - lane));
+        s_k0[w][slot] = cell_start[cn];
+        s_pre[w][slot] = cell_start[cn + 1] - cell_start[cn];  // lengths for now
+        const uint32_t code = image_code(sx, sy, sz);
+        s_code[w][slot] = (int32_t)code;
+        // mixed lists: d = c_i - c_j - s nc = -o
+        s_ecode[w][slot] = (int32_t)(dcode ? image_code(-ox, -oy, -oz) : code);
       }
-      s_pre[w][27] = acc;
-    }
-    wave_lds_sync();
-  } else {
-    // staged path: pieces by neighbour rows; lane q < 9 builds neighbour row q
-    // (dz = q/3 - 1, dy = q%3 - 1)
-    if (lane < 9) {
-      int32_t nz, sz, ny, sy;
-      stencil_axis(qz, lane / 3 - 1, nc, nz, sz);
-      stencil_axis(qy, lane % 3 - 1, nc, ny, sy);
-      const int32_t rowbase = R.coff + (nz * nc + ny) * nc;
-      const int p = 3 * lane;
-      // left wrap, main, right wrap; empty pieces have zero length
-      s_k0[w][p] = cell_start[rowbase + nc - 1];
-      s_code[w][p] = (int32_t)image_code(-1, sy, sz);
-      const int32_t nl = qx - 1 < 0 ? cell_start[rowbase + nc] - cell_start[rowbase + nc - 1] : 0;
-      const int32_t lo = qx - 1 < 0 ? 0 : qx - 1, hi = qx + 1 >= nc ? nc - 1 : qx + 1;
-      s_k0[w][p + 1] = cell_start[rowbase + lo];
-      s_code[w][p + 1] = (int32_t)image_code(0, sy, sz);
-      const int32_t nm = cell_start[rowbase + hi + 1] - cell_start[rowbase + lo];
-      s_k0[w][p + 2] = cell_start[rowbase];
-      s_code[w][p + 2] = (int32_t)image_code(1, sy, sz);
-      const int32_t nr = qx + 1 >= nc ? cell_start[rowbase + 1] - cell_start[rowbase] : 0;
-      s_pre[w][p] = nl;  // lengths for now
-      s_pre[w][p + 1] = nm;
-      s_pre[w][p + 2] = nr;
-      // the tile's row q: left piece (logical cell a-1 < 0), main cells, right
-      // piece (logical cell a+nx >= nc); offsets of this cell's pieces in it
-      const RowTile T = rtiles[cell_tile[c]];
-      const int32_t tlo = T.a - 1, thi = T.a + T.nx;
-      const int32_t mlo = tlo < 0 ? 0 : tlo, mhi = thi >= nc ? nc - 1 : thi;
-      const int32_t lsz = tlo < 0 ? cell_start[rowbase + nc] - cell_start[rowbase + nc - 1] : 0;
-      const int32_t msz = cell_start[rowbase + mhi + 1] - cell_start[rowbase + mlo];
-      const int32_t rsz = thi >= nc ? cell_start[rowbase + 1] - cell_start[rowbase] : 0;
-      s_rowsz[w][lane] = lsz + msz + rsz;
-      s_l0[w][p] = 0;
-      s_l0[w][p + 1] = lsz + (cell_start[rowbase + lo] - cell_start[rowbase + mlo]);
-      s_l0[w][p + 2] = lsz + msz;
-    }
-    __builtin_amdgcn_wave_barrier();
-    if (lane == 0) {
-      int32_t acc = 0;
-      for (int p = 0; p < 27; ++p) {
-        const int32_t len = s_pre[w][p];
-        s_pre[w][p] = acc;
-        acc += len;
-      }
-      s_pre[w][27] = acc;
-      int32_t ro = 0;
-      for (int q = 0; q < 9; ++q) {
-        for (int u = 0; u < 3; ++u) s_l0[w][3 * q + u] += ro;
-        ro += s_rowsz[w][q];
-      }
-      if (ro > kMaxStaged) atomicOr(&st->err, kErrSlots);
-    }
-    __builtin_amdgcn_wave_barrier();
-  }
-  const int32_t ncand = s_pre[w][27];
-
-  // groups of at most kCwGroup home particles, of equal size
-  const int32_t ngrp = (nh + kCwGroup - 1) / kCwGroup;
-  const int32_t gsz = ngrp ? (nh + ngrp - 1) / ngrp : 1;
-  // first packed candidate of the cell's own particles (the home cell's
-  // piece, or the main piece of the central row: the only candidates that
-  // can be a home particle itself)
-  const int32_t sv0 = s_pre[w][own_slot] + (h0 - s_k0[w][own_slot]);
-  for (int32_t g0 = 0; g0 < nh; g0 += gsz) {
-    const int32_t gn = nh - g0 < gsz ? nh - g0 : gsz;
-    const int32_t gbase = __builtin_amdgcn_readfirstlane(h0 + g0);  // wave-uniform
-    E* const grow = nbr + list_base(gbase, cap);
-    const int32_t gs0 = sv0 + g0;  // packed candidates of the group's own particles: [gs0, gs0 + gn)
-    int32_t cntv = 0;              // lane h: hits of home gbase + h so far
-    for (int32_t pb = 0; pb < ncand; pb += kCwChunks * 64) {
-      const int32_t pend = ncand - pb < kCwChunks * 64 ? ncand : pb + kCwChunks * 64;
-      const int32_t nwords = 2 * ((pend - pb + 63) >> 6);
-      int32_t passv = 0;  // lane h: hits of home gbase + h in this pass
-      // ---- test phase ----
-      for (int32_t base = pb; base < pend; base += 64) {
-        const int32_t ci = (base - pb) >> 6;
-        const int32_t v = base + lane;
-        const bool valid = v < ncand;
-        // piece of candidate v: the last p with s_pre[p] <= v
-        int p = 0;
-#pragma unroll
-        for (int step = 16; step >= 1; step >>= 1)
-          if (p + step <= 26 && s_pre[w][p + step] <= v) p += step;
-        const int32_t k = valid ? s_k0[w][p] + (v - s_pre[w][p]) : h0;
-        const uint32_t code = (uint32_t)s_code[w][p];
-        const double4 q = pos_tmp[k];
-        // the periodic shift of the piece, added after the difference:
-        // d = (x_j - x_i) + s L (exactly antisymmetric under exchange); a
-        // chunk with no shifted candidate skips the adds (x + 0 = x up to
-        // the sign of a zero, which r^2 does not see).  Lanes past the last
-        // candidate sit far away, so their test fails without a mask.
-        const double sx = (double)(((int32_t)(code << 4)) >> 30) * R.L;
-        const double sy = (double)(((int32_t)(code << 2)) >> 30) * R.L;
-        const double sz = (double)(((int32_t)code) >> 30) * R.L;
-        const double xq = valid ? q.x : kFar, yq = q.y, zq = q.z;
-        const bool shifted = __builtin_amdgcn_ballot_w64(valid && code != 0u) != 0;
-        const int32_t tj = (int32_t)q.w;  // thr[4 ta + tj] is the pair (ta, tj)
-        const double t0 = s_thr[tj], t1 = s_thr[4 + tj], t2 = s_thr[8 + tj], t3 = s_thr[12 + tj];
-        const double d01 = t1 - t0;
-        uint32_t entry;
-        if constexpr (TILE) {
-          entry = (uint32_t)((s_l0[w][p] + (v - s_pre[w][p])) & 0x3fff) | ((uint32_t)tj << 14);
-        } else {
-          entry = (uint32_t)k | (uint32_t)s_ecode[w][p];
+      own_slot = 0;
+      wave_lds_sync();
+      if (lane == 0) {
+        int32_t acc = 0;
+        for (int p = 0; p < 27; ++p) {
+          const int32_t len = s_pre[w][p];
+          s_pre[w][p] = acc;
+          acc += len;
         }
-        ent[ci * 64 + lane] = entry;
-        // chunks that miss the group's own particles skip the self test
-        const bool self_chunk = base < gs0 + gn && gs0 < base + 64;
-        uint32_t mlo = 0, mhi = 0;  // lane h: hit bits of home gbase + h
-        int32_t h = 0;
-        // U home particles (wave-uniform, scalar loads): the distances
-        // first (independent work), then the ballots; blocks of HPI, then
-        // one of 2 and one of 1 for the rest, all with the same code
-        auto block = [&](auto self_tag, auto shift_tag, auto u_tag) {
-          constexpr bool SELF = decltype(self_tag)::value;
-          constexpr bool SHIFT = decltype(shift_tag)::value;
-          constexpr int U = decltype(u_tag)::value;
-          const int32_t i0 = __builtin_amdgcn_readfirstlane(gbase + h);
-          double ra[U], tha[U];
-#pragma unroll
-          for (int u = 0; u < U; ++u) {
-            const double4 pa = pos_tmp[i0 + u];
-            double ax = xq - pa.x, ay = yq - pa.y, az = zq - pa.z;
-            if constexpr (SHIFT) {
-              ax = ax + sx;
-              ay = ay + sy;
-              az = az + sz;
-            }
-            ra[u] = (ax * ax + ay * ay) + az * az;
-            tha[u] = pick_thr<NT>(pa.w, t0, d01, t1, t2, t3);
-          }
-          uint64_t m[U];
-#pragma unroll
-          for (int u = 0; u < U; ++u) {
-            const bool hit = SELF ? ((k != i0 + u) & (ra[u] < tha[u])) : ra[u] < tha[u];
-            m[u] = __builtin_amdgcn_ballot_w64(hit);
-          }
-          write_lanes<U>(mlo, mhi, m, h);
-          h += U;
-        };
-        auto homes = [&](auto self_tag, auto shift_tag) {
-          while (h + HPI <= gn) block(self_tag, shift_tag, std::integral_constant<int, HPI>{});
-          if (h + 2 <= gn) block(self_tag, shift_tag, std::integral_constant<int, 2>{});
-          if (h < gn) block(self_tag, shift_tag, std::integral_constant<int, 1>{});
-        };
-        if (shifted) {
-          if (self_chunk)
-            homes(std::true_type{}, std::true_type{});
-          else
-            homes(std::false_type{}, std::true_type{});
-        } else {
-          if (self_chunk)
-            homes(std::true_type{}, std::false_type{});
-          else
-            homes(std::false_type{}, std::false_type{});
-        }
-        if (lane < kCwGroup) {
-          hits[(2 * ci) * kCwGroup + lane] = mlo;
-          hits[(2 * ci + 1) * kCwGroup + lane] = mhi;
-        }
-        passv += (int32_t)(__popc(mlo) + __popc(mhi));  // 0 on lanes >= gn
+        s_pre[w][27] = acc;
       }
       wave_lds_sync();
-      // ---- write phase ----
-      // home h = lane & 31 stores its first lim rows of the pass, from row
-      // cntv on: lane h the first S of them, lane h + 32 the rest (S = half
-      // the longest), each lane walking the home's hit bits from its first
-      // rank on.  Both halves store whole row segments.
-      const int32_t room = cap - cntv > 0 ? cap - cntv : 0;
-      const int32_t lim = lane < gn ? (passv < room ? passv : room) : 0;
-      int32_t mxl = lim;
+    } else {
+      // staged path: pieces by neighbour rows; lane q < 9 builds neighbour row q
+      // (dz = q/3 - 1, dy = q%3 - 1)
+      if (lane < 9) {
+        int32_t nz, sz, ny, sy;
+        stencil_axis(qz, lane / 3 - 1, nc, nz, sz);
+        stencil_axis(qy, lane % 3 - 1, nc, ny, sy);
+        const int32_t rowbase = R.coff + (nz * nc + ny) * nc;
+        const int p = 3 * lane;
+        // left wrap, main, right wrap; empty pieces have zero length
+        s_k0[w][p] = cell_start[rowbase + nc - 1];
+        s_code[w][p] = (int32_t)image_code(-1, sy, sz);
+        const int32_t nl = qx - 1 < 0 ? cell_start[rowbase + nc] - cell_start[rowbase + nc - 1] : 0;
+        const int32_t lo = qx - 1 < 0 ? 0 : qx - 1, hi = qx + 1 >= nc ? nc - 1 : qx + 1;
+        s_k0[w][p + 1] = cell_start[rowbase + lo];
+        s_code[w][p + 1] = (int32_t)image_code(0, sy, sz);
+        const int32_t nm = cell_start[rowbase + hi + 1] - cell_start[rowbase + lo];
+        s_k0[w][p + 2] = cell_start[rowbase];
+        s_code[w][p + 2] = (int32_t)image_code(1, sy, sz);
+        const int32_t nr = qx + 1 >= nc ? cell_start[rowbase + 1] - cell_start[rowbase] : 0;
+        s_pre[w][p] = nl;  // lengths for now
+        s_pre[w][p + 1] = nm;
+        s_pre[w][p + 2] = nr;
+        // the tile's row q: left piece (logical cell a-1 < 0), main cells, right
+        // piece (logical cell a+nx >= nc); offsets of this cell's pieces in it
+        const RowTile T = rtiles[cell_tile[c]];
+        const int32_t tlo = T.a - 1, thi = T.a + T.nx;
+        const int32_t mlo = tlo < 0 ? 0 : tlo, mhi = thi >= nc ? nc - 1 : thi;
+        const int32_t lsz = tlo < 0 ? cell_start[rowbase + nc] - cell_start[rowbase + nc - 1] : 0;
+        const int32_t msz = cell_start[rowbase + mhi + 1] - cell_start[rowbase + mlo];
+        const int32_t rsz = thi >= nc ? cell_start[rowbase + 1] - cell_start[rowbase] : 0;
+        s_rowsz[w][lane] = lsz + msz + rsz;
+        s_l0[w][p] = 0;
+        s_l0[w][p + 1] = lsz + (cell_start[rowbase + lo] - cell_start[rowbase + mlo]);
+        s_l0[w][p + 2] = lsz + msz;
+      }
+      __builtin_amdgcn_wave_barrier();
+      if (lane == 0) {
+        int32_t acc = 0;
+        for (int p = 0; p < 27; ++p) {
+          const int32_t len = s_pre[w][p];
+          s_pre[w][p] = acc;
+          acc += len;
+        }
+        s_pre[w][27] = acc;
+        int32_t ro = 0;
+        for (int q = 0; q < 9; ++q) {
+          for (int u = 0; u < 3; ++u) s_l0[w][3 * q + u] += ro;
+          ro += s_rowsz[w][q];
+        }
+        if (ro > kMaxStaged) atomicOr(&st->err, kErrSlots);
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
+    const int32_t ncand = s_pre[w][27];
+
+    // groups of at most kCwGroup home particles, of equal size
+    const int32_t ngrp = (nh + kCwGroup - 1) / kCwGroup;
+    const int32_t gsz = ngrp ? (nh + ngrp - 1) / ngrp : 1;
+    // first packed candidate of the cell's own particles (the home cell's
+    // piece, or the main piece of the central row: the only candidates that
+    // can be a home particle itself)
+    const int32_t sv0 = s_pre[w][own_slot] + (h0 - s_k0[w][own_slot]);
+    for (int32_t g0 = 0; g0 < nh; g0 += gsz) {
+      const int32_t gn = nh - g0 < gsz ? nh - g0 : gsz;
+      const int32_t gbase = __builtin_amdgcn_readfirstlane(h0 + g0);  // wave-uniform
+      E* const grow = nbr + list_base(gbase, cap);
+      const int32_t gs0 = sv0 + g0;  // packed candidates of the group's own particles: [gs0, gs0 + gn)
+      int32_t cntv = 0;              // lane h: hits of home gbase + h so far
+      for (int32_t pb = 0; pb < ncand; pb += kCwChunks * 64) {
+        const int32_t pend = ncand - pb < kCwChunks * 64 ? ncand : pb + kCwChunks * 64;
+        const int32_t nwords = 2 * ((pend - pb + 63) >> 6);
+        int32_t passv = 0;  // lane h: hits of home gbase + h in this pass
+        // ---- test phase ----
+        for (int32_t base = pb; base < pend; base += 64) {
+          const int32_t ci = (base - pb) >> 6;
+          const int32_t v = base + lane;
+          const bool valid = v < ncand;
+          // piece of candidate v: the last p with s_pre[p] <= v
+          int p = 0;
 #pragma unroll
-      for (int d = 32; d >= 1; d >>= 1) mxl = max(mxl, __shfl_xor(mxl, d, 64));
-      const int32_t half = (__builtin_amdgcn_readfirstlane(mxl) + 1) >> 1;
-      const int32_t hl = lane & (kCwGroup - 1), seg = lane >> 5;
-      const int32_t lim_h = __shfl(lim, hl, 64), cnt_h = __shfl(cntv, hl, 64);
-      const int32_t rbeg = seg ? half : 0;
-      const int32_t nseg = (seg ? lim_h : (lim_h < half ? lim_h : half)) - rbeg;
-      int32_t wi = 0;
-      uint32_t cur = 0u;
-      if (nseg > 0) {
-        cur = hits[hl];
-        if (seg) {
-          // the word holding the home's hit of rank rbeg, then that bit
-          int32_t acc = 0, pc = __popc(cur);
-          while (acc + pc <= rbeg && wi + 1 < nwords) {
-            acc += pc;
-            ++wi;
-            cur = hits[wi * kCwGroup + hl];
-            pc = __popc(cur);
+          for (int step = 16; step >= 1; step >>= 1)
+            if (p + step <= 26 && s_pre[w][p + step] <= v) p += step;
+          const int32_t k = valid ? s_k0[w][p] + (v - s_pre[w][p]) : h0;
+          const uint32_t code = (uint32_t)s_code[w][p];
+          const double4 q = pos_tmp[k];
+          // the periodic shift of the piece, added after the difference:
+          // d = (x_j - x_i) + s L (exactly antisymmetric under exchange); a
+          // chunk with no shifted candidate skips the adds (x + 0 = x up to
+          // the sign of a zero, which r^2 does not see).  Lanes past the last
+          // candidate sit far away, so their test fails without a mask.
+          const double sx = (double)(((int32_t)(code << 4)) >> 30) * R.L;
+          const double sy = (double)(((int32_t)(code << 2)) >> 30) * R.L;
+          const double sz = (double)(((int32_t)code) >> 30) * R.L;
+          const double xq = valid ? q.x : kFar, yq = q.y, zq = q.z;
+          const bool shifted = __builtin_amdgcn_ballot_w64(valid && code != 0u) != 0;
+          const int32_t tj = (int32_t)q.w;  // thr[4 ta + tj] is the pair (ta, tj)
+          const double t0 = s_thr[tj], t1 = s_thr[4 + tj], t2 = s_thr[8 + tj], t3 = s_thr[12 + tj];
+          const double d01 = t1 - t0;
+          uint32_t entry;
+          if constexpr (TILE) {
+            entry = (uint32_t)((s_l0[w][p] + (v - s_pre[w][p])) & 0x3fff) | ((uint32_t)tj << 14);
+          } else {
+            entry = (uint32_t)k | (uint32_t)s_ecode[w][p];
           }
-          for (int32_t j = acc; j < rbeg; ++j) cur &= cur - 1u;
+          ent[ci * 64 + lane] = entry;
+          // chunks that miss the group's own particles skip the self test
+          const bool self_chunk = base < gs0 + gn && gs0 < base + 64;
+          uint32_t mlo = 0, mhi = 0;  // lane h: hit bits of home gbase + h
+          int32_t h = 0;
+          // U home particles (wave-uniform, scalar loads): the distances
+          // first (independent work), then the ballots; blocks of HPI, then
+          // one of 2 and one of 1 for the rest, all with the same code
+          auto block = [&](auto self_tag, auto shift_tag, auto u_tag) {
+            constexpr bool SELF = decltype(self_tag)::value;
+            constexpr bool SHIFT = decltype(shift_tag)::value;
+            constexpr int U = decltype(u_tag)::value;
+            const int32_t i0 = __builtin_amdgcn_readfirstlane(gbase + h);
+            double ra[U], tha[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+              const double4 pa = pos_tmp[i0 + u];
+              double ax = xq - pa.x, ay = yq - pa.y, az = zq - pa.z;
+              if constexpr (SHIFT) {
+                ax = ax + sx;
+                ay = ay + sy;
+                az = az + sz;
+              }
+              ra[u] = (ax * ax + ay * ay) + az * az;
+              tha[u] = pick_thr<NT>(pa.w, t0, d01, t1, t2, t3);
+            }
+            uint64_t m[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+              const bool hit = SELF ? ((k != i0 + u) & (ra[u] < tha[u])) : ra[u] < tha[u];
+              m[u] = __builtin_amdgcn_ballot_w64(hit);
+            }
+            write_lanes<U>(mlo, mhi, m, h);
+            h += U;
+          };
+          auto homes = [&](auto self_tag, auto shift_tag) {
+            while (h + HPI <= gn) block(self_tag, shift_tag, std::integral_constant<int, HPI>{});
+            if (h + 2 <= gn) block(self_tag, shift_tag, std::integral_constant<int, 2>{});
+            if (h < gn) block(self_tag, shift_tag, std::integral_constant<int, 1>{});
+          };
+          if (shifted) {
+            if (self_chunk)
+              homes(std::true_type{}, std::true_type{});
+            else
+              homes(std::false_type{}, std::true_type{});
+          } else {
+            if (self_chunk)
+              homes(std::true_type{}, std::false_type{});
+            else
+              homes(std::false_type{}, std::false_type{});
+          }
+          if (lane < kCwGroup) {
+            hits[(2 * ci) * kCwGroup + lane] = mlo;
+            hits[(2 * ci + 1) * kCwGroup + lane] = mhi;
+          }
+          passv += (int32_t)(__popc(mlo) + __popc(mhi));  // 0 on lanes >= gn
         }
-      }
-      // list slot of home gbase + hl relative to grow (a group of at most 32
-      // consecutive particles spans at most two slices)
-      const uint32_t hslot =
-          (uint32_t)hl +
-          (((gbase & (kSlice - 1)) + hl) >= kSlice ? (uint32_t)(cap - 1) * (uint32_t)kSlice : 0u);
-      const uint32_t loff = hslot + (uint32_t)(cnt_h + rbeg) * (uint32_t)kSlice;
-      // lane: rows [0, nseg) of its segment.  An iteration stores the next
-      // row; when the lane's word is used up it first takes the word read
-      // ahead, and the word after that is read with no select on its value,
-      // so that read stays in flight beside the entry read instead of being
-      // waited for (t < nseg leaves a set bit in words wi.., so a refill
-      // never passes the last word; the clamp on wi and the spare word only
-      // keep every access inside the wave's arrays).  A lane that meets an
-      // empty word (rare) spends an iteration on it and stores its later
-      // rows one iteration late; every lane is done within half + nwords
-      // iterations (at most half rows, at most one word change per word).
-      uint32_t nxt = hits[(wi + 1) * kCwGroup + hl];
-      const uint32_t* ew = ent + wi * 32;  // entries of the current word
-      E* rowp = grow + loff;               // the lane's next row slot
-      int32_t r = 0;
-      const int32_t tmax = half + nwords;
-      for (int32_t t = 0; t < tmax; ++t) {
-        if (!__builtin_amdgcn_ballot_w64(r < nseg)) break;
-        if (r < nseg) {
-          if (cur == 0u) {
-            wi = wi + 1 < nwords ? wi + 1 : wi;
-            ew = ent + wi * 32;
-            // the copy as an instruction of its own, kept above the read:
-            // the new word then lands in nxt's own register and nothing
-            // waits for it here
-            asm volatile("v_mov_b32 %0, %1" : "=v"(cur) : "v"(nxt));
-            __builtin_amdgcn_sched_barrier(0);
-            nxt = hits[(wi + 1) * kCwGroup + hl];
-          }
-          if (cur != 0u) {
-            const uint32_t b = (uint32_t)__builtin_ctz(cur);
-            cur &= cur - 1u;
-            *rowp = (E)ew[b];
-            rowp += kSlice;
-            ++r;
+        wave_lds_sync();
+        // ---- write phase ----
+        // home h = lane & 31 stores its first lim rows of the pass, from row
+        // cntv on: lane h the first S of them, lane h + 32 the rest (S = half
+        // the longest), each lane walking the home's hit bits from its first
+        // rank on.  Both halves store whole row segments.
+        const int32_t room = cap - cntv > 0 ? cap - cntv : 0;
+        const int32_t lim = lane < gn ? (passv < room ? passv : room) : 0;
+        int32_t mxl = lim;
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) mxl = max(mxl, __shfl_xor(mxl, d, 64));
+        const int32_t half = (__builtin_amdgcn_readfirstlane(mxl) + 1) >> 1;
+        const int32_t hl = lane & (kCwGroup - 1), seg = lane >> 5;
+        const int32_t lim_h = __shfl(lim, hl, 64), cnt_h = __shfl(cntv, hl, 64);
+        const int32_t rbeg = seg ? half : 0;
+        const int32_t nseg = (seg ? lim_h : (lim_h < half ? lim_h : half)) - rbeg;
+        int32_t wi = 0;
+        uint32_t cur = 0u;
+        if (nseg > 0) {
+          cur = hits[hl];
+          if (seg) {
+            // the word holding the home's hit of rank rbeg, then that bit
+            int32_t acc = 0, pc = __popc(cur);
+            while (acc + pc <= rbeg && wi + 1 < nwords) {
+              acc += pc;
+              ++wi;
+              cur = hits[wi * kCwGroup + hl];
+              pc = __popc(cur);
+            }
+            for (int32_t j = acc; j < rbeg; ++j) cur &= cur - 1u;
           }
         }
+        // list slot of home gbase + hl relative to grow (a group of at most 32
+        // consecutive particles spans at most two slices)
+        const uint32_t hslot =
+            (uint32_t)hl +
+            (((gbase & (kSlice - 1)) + hl) >= kSlice ? (uint32_t)(cap - 1) * (uint32_t)kSlice : 0u);
+        const uint32_t loff = hslot + (uint32_t)(cnt_h + rbeg) * (uint32_t)kSlice;
+        // lane: rows [0, nseg) of its segment.  An iteration stores the next
+        // row; when the lane's word is used up it first takes the word read
+        // ahead, and the word after that is read with no select on its value,
+        // so that read stays in flight beside the entry read instead of being
+        // waited for (t < nseg leaves a set bit in words wi.., so a refill
+        // never passes the last word; the clamp on wi and the spare word only
+        // keep every access inside the wave's arrays).  A lane that meets an
+        // empty word (rare) spends an iteration on it and stores its later
+        // rows one iteration late; every lane is done within half + nwords
+        // iterations (at most half rows, at most one word change per word).
+        uint32_t nxt = hits[(wi + 1) * kCwGroup + hl];
+        const uint32_t* ew = ent + wi * 32;  // entries of the current word
+        E* rowp = grow + loff;               // the lane's next row slot
+        int32_t r = 0;
+        const int32_t tmax = half + nwords;
+        for (int32_t t = 0; t < tmax; ++t) {
+          if (!__builtin_amdgcn_ballot_w64(r < nseg)) break;
+          if (r < nseg) {
+            if (cur == 0u) {
+              wi = wi + 1 < nwords ? wi + 1 : wi;
+              ew = ent + wi * 32;
+              // the copy as an instruction of its own, kept above the read:
+              // the new word then lands in nxt's own register and nothing
+              // waits for it here
+              asm volatile("v_mov_b32 %0, %1" : "=v"(cur) : "v"(nxt));
+              __builtin_amdgcn_sched_barrier(0);
+              nxt = hits[(wi + 1) * kCwGroup + hl];
+            }
+            if (cur != 0u) {
+              const uint32_t b = (uint32_t)__builtin_ctz(cur);
+              cur &= cur - 1u;
+              *rowp = (E)ew[b];
+              rowp += kSlice;
+              ++r;
+            }
+          }
+        }
+        cntv += passv;
+        wave_lds_sync();  // the next pass or group rewrites ent and hits
       }
-      cntv += passv;
-      wave_lds_sync();  // the next pass or group rewrites ent and hits
+      if (lane < gn) {
+        ncount[gbase + lane] = cntv;
+        if (cntv > cap) atomicOr(&st->err, kErrOverflow);
+      }
     }
-    if (lane < gn) {
-      ncount[gbase + lane] = cntv;
-      if (cntv > cap) atomicOr(&st->err, kErrOverflow);
+    // the new cell order becomes the live state
+    for (int32_t h = lane; h < nh; h += 64) {
+      const int32_t i = h0 + h;
+      const double4 p4 = pos_tmp[i];
+      if (pos16)
+        pos16[i] = make_recq(p4.x, p4.y, p4.z, pack_cell(qx, qy, qz, (int32_t)p4.w), R.cside, R.qs);
+      pos[i] = p4;
+      xref[i] = p4.x;
+      xref[stride + i] = p4.y;
+      xref[2 * (size_t)stride + i] = p4.z;
+      vel[i] = vel_tmp[i];
+      vel[stride + i] = vel_tmp[stride + i];
+      vel[2 * (size_t)stride + i] = vel_tmp[2 * (size_t)stride + i];
+      id[i] = id_tmp[i];
     }
-  }
-  // the new cell order becomes the live state
-  for (int32_t h = lane; h < nh; h += 64) {
-    const int32_t i = h0 + h;
-    const double4 p4 = pos_tmp[i];
-    if (pos16)
-      pos16[i] = make_recq(p4.x, p4.y, p4.z, pack_cell(qx, qy, qz, (int32_t)p4.w), R.cside, R.qs);
-    pos[i] = p4;
-    xref[i] = p4.x;
-    xref[stride + i] = p4.y;
-    xref[2 * (size_t)stride + i] = p4.z;
-    vel[i] = vel_tmp[i];
-    vel[stride + i] = vel_tmp[stride + i];
-    vel[2 * (size_t)stride + i] = vel_tmp[2 * (size_t)stride + i];
-    id[i] = id_tmp[i];
+  };
+  for (int32_t b = blockIdx.x; b < nblk; b += gridDim.x) {
+    const int32_t c = (spread ? xcd_spread(b, spread) : xcd_block(b, nblk)) * kCwWaves + w;
+    if (c < ncells) cell(c);
+    wave_lds_sync();  // the wave's next cell rewrites its arrays
   }
 }
 
@@ -583,9 +587,9 @@ void launch_nlist(hipStream_t s, int32_t ntiles1, const Tile* tiles1, const RepD
     const int32_t nb = (ncells + kCwWaves - 1) / kCwWaves;
     const int32_t g = spread / kCwWaves, grid = g ? spread_grid(nb, g) : nb;
 #define KN(NT)                                                                             \
-  k_nlist_cells<kCwHomes, false, NT><<<grid, 64 * kCwWaves, 0, s>>>(                       \
+  k_nlist_cells<kCwHomes, false, NT><<<gated_grid(grid, g != 0), 64 * kCwWaves, 0, s>>>(           \
           ncells, cell_rep, reps, rebuild, tab, cell_start, stride, cap, pos_tmp, vel_tmp, \
-          id_tmp, pos, vel, id, xref, nbr, ncount, st, pos16, nullptr, nullptr, dcode, g)
+          id_tmp, pos, vel, id, xref, nbr, ncount, st, pos16, nullptr, nullptr, dcode, g, grid)
     if (thr_form == 2) KN(2); else KN(4);
 #undef KN
   }
@@ -605,9 +609,9 @@ void launch_nlist_tiles(hipStream_t s, int32_t ncells, const int32_t* cell_rep,
   const int32_t nb = (ncells + kCwWaves - 1) / kCwWaves;
   const int32_t g = spread / kCwWaves, grid = g ? spread_grid(nb, g) : nb;
 #define KT(NT)                                                                                   \
-  k_nlist_cells<kCwHomes, true, NT><<<grid, 64 * kCwWaves, 0, s>>>(                              \
+  k_nlist_cells<kCwHomes, true, NT><<<gated_grid(grid, g != 0), 64 * kCwWaves, 0, s>>>(                              \
           ncells, cell_rep, reps, rebuild, tab, cell_start, stride, cap, pos_tmp, vel_tmp, id_tmp, \
-          pos, vel, id, xref, nbr16, ncount, st, nullptr, cell_tile, rtiles, 0, g)
+          pos, vel, id, xref, nbr16, ncount, st, nullptr, cell_tile, rtiles, 0, g, grid)
   if (thr_form == 2) KT(2); else KT(4);
 #undef KT
 }
