@@ -26,7 +26,7 @@ COMMON = ["-O3", "-std=c++17", f"--offload-arch={ARCH}", "-fPIC", "-x", "hip",
 PER_FILE = {"nlist.hip": ["-ffp-contract=off"], "nlist_small.hip": ["-ffp-contract=off"],
             "nlist_brick.hip": ["-ffp-contract=off", "-fno-honor-nans"], "analysis.hip": ["-ffp-contract=off"]}
 SOURCES = ["cells.hip", "nlist.hip", "nlist_small.hip", "nlist_brick.hip", "force.hip",
-           "force_brick.hip", "force_staged.hip", "force_cells.hip", "integrate.hip",
+           "force_brick.hip", "force_search.hip", "force_staged.hip", "force_cells.hip", "integrate.hip",
            "analysis.hip", "md_api.cpp"]
 
 

@@ -45,6 +45,7 @@ struct BrickTile {
   int32_t tx, ty, tz;   // home cells per axis, 1 .. 4
   int32_t units;        // partials of the tile: 1, or kTileUnits of kUnitHomes homes each
   int32_t part;         // its first partial
+  int32_t b0, nb;       // its bricks
 };
 struct Brick {
   int32_t tile;

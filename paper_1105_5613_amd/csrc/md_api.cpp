@@ -57,6 +57,9 @@ struct md_ctx_s {
   int32_t cells = 0;  // list-free cell path (row tiles, no neighbour list)
   // brick path (brick.h): what MD_PATH_AUTO runs where it can (plan_bricks)
   bool brick = false;
+  // list-free path on the same tiles (force_search.hip)
+  bool search = false;
+  int32_t search_threads = 0;
   std::vector<BrickTile> btiles_h;
   std::vector<Brick> bricks_h;
   BrickArgs ba{};
@@ -323,6 +326,10 @@ void launch_forces(md_ctx c, int32_t mode, hipStream_t s, int32_t energy = 1,
     launch_force_brick(s, c->mixed, mode, energy, c->tpp, brick_threads(c), c->bp_h.four, c->ba,
                        c->reps, c->tab, c->bp, c->pos, c->vel, c->frc, c->stride, c->p.dt,
                        c->part, c->st, FuseOut{c->pos_tmp, nullptr, c->xref, c->counts, nzero});
+  else if (c->search)
+    launch_force_search(s, c->mixed, mode, energy, c->search_threads, c->bp_h.four, c->ba, c->reps,
+                        c->tab, c->bp, c->cell_start, c->pos, c->vel, c->frc, c->stride, c->p.dt,
+                        c->part, c->st, FuseOut{c->pos_tmp, nullptr, c->xref, c->counts, nzero});
   else if (c->cells)
     launch_force_cells(s, c->mixed, mode, c->rc2_form, c->nrt, c->rtiles, c->reps, c->tab,
                        c->cell_start, c->pos, c->vel, c->frc, c->stride, c->p.dt, c->part,
@@ -385,11 +392,16 @@ BrickPair brick_pair(const md_params& p, const PairTab& t) {
   return b;
 }
 
-// Whether the context takes the brick path, and its tiles and bricks.
-// Conditions: MD_PATH_AUTO with no force variant asked for by tpp or unroll
-// (those name gather variants), at least three cells per side in every
-// replica, parameters whose r^-12 coefficient is an ordinary double, and in
-// every replica 27 cells that fit the LDS slots.
+// Whether the context takes the brick path, or on MD_PATH_CELLS the search on
+// tiles of cells, and its tiles and bricks.  Conditions: MD_PATH_AUTO with no
+// force variant asked for by tpp or unroll (those name gather variants), or
+// MD_PATH_CELLS with no row tile asked for by tile_cells; at least three cells
+// per side in every replica, parameters whose r^-12 coefficient is an ordinary
+// double, and in every replica 27 cells that fit the LDS slots.  (The search
+// keeps to the smaller LDS layout, two blocks of which leave room for its
+// words, and spares 6 %: a tile that outgrows it costs one rebuild.  20 steps
+// without lists at 1,372 / 20,000 / 1,048,576 particles FP64: 74 / 65 / 441 us
+// a step, by row tiles 278 / 269 / 1,397.)
 //
 // Tiles: the most home cells (up to 4 per axis) whose expected neighbourhood
 // fits the slots with 12 % to spare and whose homes fit one or two rounds of
@@ -400,28 +412,36 @@ BrickPair brick_pair(const md_params& p, const PairTab& t) {
 // same alone and in a batch.
 bool plan_bricks(md_ctx c) {
   const md_params& p = c->p;
-  if (p.path != MD_PATH_AUTO || p.tpp != 0 || p.unroll != 0) return false;
+  const bool cells = c->cells;  // for the list-free search
+  if (cells ? p.tile_cells != 0 : p.path != MD_PATH_AUTO || p.tpp != 0 || p.unroll != 0)
+    return false;
   for (int a = 0; a < p.ntypes; ++a)
     for (int b = 0; b < p.ntypes; ++b) {
       const double s = p.sig[a * MD_MAXT + b], e = std::fabs(p.eps[a * MD_MAXT + b]);
       if (s < 1e-15 || s > 1e15 || (e != 0.0 && (e < 1e-60 || e > 1e60))) return false;
     }
-  auto slots = [](double ppc, int x, int y, int z) {
-    return 1.12 * ppc * (x + 2) * (y + 2) * (z + 2) + 48.0;
+  const double spare = cells ? 1.06 : 1.12;
+  const int32_t most = cells ? kBrickSlots : kBrickSlotsBig;
+  auto slots = [&](double ppc, int x, int y, int z) {
+    return spare * ppc * (x + 2) * (y + 2) * (z + 2) + 48.0;
   };
   for (const RepDesc& d : c->reps_h) {
     if (d.nc < 3) return false;
     // short lists: the copy of the neighbourhood is not earned back (the
-    // soft-sphere box, 15 entries: 57 us by gathers, 96 by bricks)
+    // soft-sphere box, 15 entries: 57 us by gathers, 96 by bricks; without
+    // lists the search is the faster form there too, 20 steps of 1,048,576
+    // particles in 6,360 us against 10,510)
     const double side = max_rc(p) + p.skin;
-    if ((double)d.n / d.volume * 4.0 / 3.0 * M_PI * side * side * side < 48.0) return false;
-    if (slots((double)d.n / ((double)d.nc * d.nc * d.nc), 1, 1, 1) >= kBrickSlotsBig) return false;
+    if (!cells && (double)d.n / d.volume * 4.0 / 3.0 * M_PI * side * side * side < 48.0)
+      return false;
+    if (slots((double)d.n / ((double)d.nc * d.nc * d.nc), 1, 1, 1) >= most) return false;
   }
   c->btiles_h.clear();
   c->bricks_h.clear();
   c->brick_parts = 0;
   c->ba = BrickArgs{};
   bool big = false;
+  int32_t bricks = 1;  // most of a tile
   for (int32_t r = 0; r < c->nrep; ++r) {
     RepDesc& d = c->reps_h[r];
     const int32_t nc = d.nc;
@@ -432,7 +452,7 @@ bool plan_bricks(md_ctx c) {
       for (int y = 1; y <= x; ++y)
         for (int z = 1; z <= y; ++z) {
           const double homes = ppc * x * y * z;
-          if (homes > 240.0 || slots(ppc, x, y, z) >= kBrickSlotsBig) continue;
+          if (homes > 240.0 || slots(ppc, x, y, z) >= most) continue;
           const int v = x * y * z, bv = bx * by * bz;
           const int h = (x + 2) * (y + 2) * (z + 2), bh = (bx + 2) * (by + 2) * (bz + 2);
           if (v > bv || (v == bv && h < bh)) bx = x, by = y, bz = z;
@@ -461,7 +481,7 @@ bool plan_bricks(md_ctx c) {
       return (int32_t)((int64_t)n * k / parts);
     };
     const int32_t ntx = (int32_t)per(bx), nty = (int32_t)per(by), ntz = (int32_t)per(bz);
-    const int32_t units = (int64_t)ntx * nty * ntz <= 256 ? kTileUnits : 1;
+    const int32_t units = !cells && (int64_t)ntx * nty * ntz <= 256 ? kTileUnits : 1;
     for (int32_t z = 0; z < ntz; ++z)
       for (int32_t y = 0; y < nty; ++y)
         for (int32_t x = 0; x < ntx; ++x) {
@@ -483,6 +503,9 @@ bool plan_bricks(md_ctx c) {
           c->brick_homes = std::max(c->brick_homes, ppc * t.tx * t.ty * t.tz);
           auto n = [](int32_t t, int32_t h) { return (t + h - 1) / h; };
           const int32_t ax = n(t.tx, hx), ay = n(t.ty, hy), az = n(t.tz, hz);
+          c->btiles_h[id].b0 = (int32_t)c->bricks_h.size();
+          c->btiles_h[id].nb = ax * ay * az;
+          bricks = std::max(bricks, ax * ay * az);
           for (int32_t k = 0; k < ax * ay * az; ++k) {
             const int32_t ix = k % ax, iy = k / ax % ay, iz = k / (ax * ay);
             Brick b{};
@@ -509,7 +532,9 @@ bool plan_bricks(md_ctx c) {
   c->ba.split = c->ba.ntiles <= 64 ? 4 : (c->ba.ntiles <= 128 ? 2 : 1);
   for (const BrickTile& t : c->btiles_h)
     if (t.units == 1) c->ba.split = 1;
-  c->brick = true;
+  c->brick = !cells;
+  c->search = cells;
+  c->search_threads = 64 * std::min(bricks, search_waves());
   return true;
 }
 
@@ -587,6 +612,17 @@ void gather_blocks(md_ctx c) {
   }
 }
 
+// ... and of the row tiles, which the replicas' tiles follow each other in.
+void row_tile_blocks(md_ctx c) {
+  int32_t t = 0;
+  for (int32_t r = 0; r < c->nrep; ++r) {
+    RepDesc& d = c->reps_h[r];
+    d.fb0 = t;
+    while (t < c->nrt && c->rtiles_h[t].rep == r) ++t;
+    d.fb1 = t;
+  }
+}
+
 md_status upload_blocks(md_ctx c) {
   plan_chunks(c);
   if (c->nchunks)
@@ -623,6 +659,16 @@ md_status leave_brick(md_ctx c) {
   return upload_blocks(c);
 }
 
+// The same on the list-free path: row tiles take any density.
+md_status leave_search(md_ctx c) {
+  HIPCHECK(c, hipStreamSynchronize(c->stream));
+  c->search = false;
+  c->ba.ntiles = 0;
+  row_tile_blocks(c);
+  drop_graph(c);
+  return upload_blocks(c);
+}
+
 // Full rebuild of every replica (md_build_cells and the first build after
 // md_set_state); grows the neighbour capacity once on overflow.
 md_status build_all(md_ctx c) {
@@ -638,8 +684,8 @@ md_status build_all(md_ctx c) {
     }
     if (rc != MD_EOVERFLOW) return rc;
     if (c->err.find("LDS slots") != std::string::npos) {  // not a capacity
-      if (!c->brick) return rc;
-      rc = leave_brick(c);
+      if (!c->brick && !c->search) return rc;
+      rc = c->brick ? leave_brick(c) : leave_search(c);
     } else {
       if (grown) return rc;
       grown = true;
@@ -704,7 +750,7 @@ void launch_forces0(md_ctx c) {
 // Directly launched NVE steps of a one-replica gather-path context can fuse
 // the next step's kick and drift into the force launch (md_params.split_kick).
 bool can_fuse(md_ctx c, int32_t thermo) {
-  return !thermo && c->nrep == 1 && !c->cells && !c->staged && c->p.split_kick == 0;
+  return !thermo && c->nrep == 1 && (!c->cells || c->search) && !c->staged && c->p.split_kick == 0;
 }
 
 // One velocity-Verlet step on stream s (also used while capturing a graph).
@@ -772,18 +818,17 @@ md_status reserve_events(md_ctx c, int32_t nsteps);
 // of this loop had its kick and drift applied by that step's force launch
 // when the call can fuse.  resume: step k0 was interrupted by an overflowed
 // list build after its kick and drift; its drift maximum is where that kick
-// left it (the previous force launch's partials for a fused direct step, the
-// kick's tile maxima otherwise).
+// left it, src = 1: the previous force launch's partials (a fused direct step),
+// 0: the kick's tile maxima.
 md_status enqueue_direct(md_ctx c, hipStream_t s, const ThermoArgs& ta, int32_t thermo,
-                         int32_t kg, int32_t k0, int32_t nsteps, bool fusable, bool resume) {
+                         int32_t k0, int32_t nsteps, bool fusable, bool resume, int32_t src) {
   md_status rc = reserve_events(c, nsteps - k0);
   if (rc) return rc;
   for (int32_t k = k0; k < nsteps; ++k) {
     const bool res = resume && k == k0;
     const bool kick = !res && !(fusable && k > k0);
-    const int32_t src = res ? (fusable && k > kg ? 1 : 0) : -1;
     rc = enqueue_step(c, s, ta, thermo, k, energy_step(ta, k, nsteps - 1), kick,
-                      fusable && k + 1 < nsteps, res, src);
+                      fusable && k + 1 < nsteps, res, res ? src : -1);
     if (rc) return rc;
   }
   return MD_OK;
@@ -1015,6 +1060,7 @@ md_status md_init_alloc(md_ctx* out, const md_params* p, int32_t nrep, const int
     const int32_t room = lds_max - 8192;  // static LDS of the kernel
     c->lcap_f = std::max(64, std::min(want, (int32_t)(room / 24)));
     if (p->stage_slots > 0) c->lcap_f = std::min(c->lcap_f, p->stage_slots);
+    if (c->cells) plan_bricks(c);
   } else if (plan_bricks(c)) {
     // lanes per particle: four fill the chip sooner (per NVE launch 32,000
     // particles FP64 24 us against 33 with two, 131,072: 42 us both), two
@@ -1063,7 +1109,7 @@ md_status md_init_alloc(md_ctx* out, const md_params* p, int32_t nrep, const int
     tab.mass[a] = a < p->ntypes ? p->mass[a] : 1.0;
     tab.inv_mass[a] = 1.0 / tab.mass[a];
   }
-  if (c->brick) c->bp_h = brick_pair(*p, tab);
+  if (c->brick || c->search) c->bp_h = brick_pair(*p, tab);
   c->thr_form = fma_pair_form(tab.thr, p->ntypes);
   c->rc2_form = fma_pair_form(tab.rc2, p->ntypes);
 
@@ -1114,7 +1160,7 @@ md_status md_init_alloc(md_ctx* out, const md_params* p, int32_t nrep, const int
   ALLOC(c->id, N);
   ALLOC(c->id_tmp, N);
   ALLOC(c->img, 3 * N);
-  if (c->brick) {
+  if (c->brick || c->search) {
     c->ba.capc = (c->cap + kChunkEntries - 1) / kChunkEntries + c->brick_extra;
     BrickTile* bt = nullptr;
     Brick* br = nullptr;
@@ -1125,9 +1171,11 @@ md_status md_init_alloc(md_ctx* out, const md_params* p, int32_t nrep, const int
     ALLOC(c->ba.head, (size_t)c->ba.ntiles);
     ALLOC(c->ba.row, (size_t)c->ba.ntiles * c->ba.rows);
     ALLOC(c->ba.hrow, (size_t)c->ba.ntiles * c->ba.hrows);
+    ALLOC(c->bp, 1);
+  }
+  if (c->brick) {
     ALLOC(c->ba.list, chunk_elems(c->ntot, c->ba.capc));
     ALLOC(c->ba.nchunk, N);
-    ALLOC(c->bp, 1);
   } else if (c->cells) {
     ALLOC(c->rtiles, (size_t)c->nrt);
   } else if (c->staged) {
@@ -1172,7 +1220,7 @@ md_status md_init_alloc(md_ctx* out, const md_params* p, int32_t nrep, const int
             up(c->tab, &tab, sizeof(PairTab)) &&
             up(c->cell_rep, cell_rep.data(), sizeof(int32_t) * c->ncells) &&
             up(c->lam, ones.data(), sizeof(double) * nrep) &&
-            (!c->brick ||
+            (!(c->brick || c->search) ||
              (up((void*)c->ba.tiles, c->btiles_h.data(), sizeof(BrickTile) * c->ba.ntiles) &&
               up((void*)c->ba.bricks, c->bricks_h.data(), sizeof(Brick) * c->ba.nbricks) &&
               up(c->bp, &c->bp_h, sizeof(BrickPair)))) &&
@@ -1330,8 +1378,8 @@ md_status md_step(md_ctx c, int32_t nsteps, const double* T0, const double* T1,
   const int32_t kg = k;  // steps [0, kg) ran inside graph replays
   // the last step of a call is never fused: the state it leaves (positions,
   // velocities, forces) is complete
-  const bool fusable = can_fuse(c, thermo);
-  md_status rc = enqueue_direct(c, s, ta, thermo, kg, kg, nsteps, fusable, false);
+  bool fusable = can_fuse(c, thermo);
+  md_status rc = enqueue_direct(c, s, ta, thermo, kg, nsteps, fusable, false, 0);
   if (rc) return rc;
   if (thermo) launch_apply_lambda(s, c->ntiles, c->tiles, c->stride, c->vel, c->lam, c->nrep, c->st);
   HIPCHECK(c, hipGetLastError());
@@ -1342,12 +1390,12 @@ md_status md_step(md_ctx c, int32_t nsteps, const double* T0, const double* T1,
     HIPCHECK(c, hipStreamSynchronize(s));
     DevState st{};
     HIPCHECK(c, hipMemcpy(&st, c->st, sizeof(DevState), hipMemcpyDeviceToHost));
-    const int32_t mend = kErrOverflow | (c->brick ? kErrSlots : 0);
+    const int32_t mend = kErrOverflow | (c->brick || c->search ? kErrSlots : 0);
     if (!(st.err & mend) || (st.err & ~mend) || attempt == 8) break;
     int64_t done = 0;
     HIPCHECK(c, hipMemcpy(&done, c->kcall, sizeof(int64_t), hipMemcpyDeviceToHost));
     if (st.err & kErrSlots) {
-      rc = leave_brick(c);
+      rc = c->brick ? leave_brick(c) : leave_search(c);
       if (!rc) {
         launch_mark_rebuild(s, c->nrep, c->rebuild, c->st);
         HIPCHECK(c, hipStreamSynchronize(s));
@@ -1363,7 +1411,11 @@ md_status md_step(md_ctx c, int32_t nsteps, const double* T0, const double* T1,
     st.err = 0;
     st.any_rebuild = 1;  // the interrupted step's rebuild flags are still set
     HIPCHECK(c, hipMemcpy(c->st, &st, sizeof(DevState), hipMemcpyHostToDevice));
-    rc = enqueue_direct(c, s, ta, thermo, kg, (int32_t)done, nsteps, fusable, true);
+    // how the interrupted step was queued, and how the rest can be: the
+    // kernels a context goes on with may not fuse (row tiles)
+    const int32_t src = fusable && (int32_t)done > kg ? 1 : 0;
+    fusable = can_fuse(c, thermo);
+    rc = enqueue_direct(c, s, ta, thermo, (int32_t)done, nsteps, fusable, true, src);
     if (rc) return rc;
     if (thermo)
       launch_apply_lambda(s, c->ntiles, c->tiles, c->stride, c->vel, c->lam, c->nrep, c->st);

@@ -406,7 +406,14 @@ void launch_nlist_tiles(hipStream_t s, int32_t ncells, const int32_t* cell_rep,
 void launch_decode_staged(hipStream_t s, int32_t nrt, const RowTile* rtiles, const RepDesc* reps,
                           const int32_t* cell_start, int32_t cap, const uint16_t* nbr,
                           const int32_t* ncount, uint32_t* out);
-// list-free cell path (force_cells.hip)
+// list-free cell path on tiles of cells (force_search.hip)
+int32_t search_waves();
+void launch_force_search(hipStream_t s, int32_t mixed, int32_t mode, int32_t energy,
+                         int32_t threads, int32_t four, const BrickArgs& A, const RepDesc* reps,
+                         const PairTab* tab, const BrickPair* bp, const int32_t* cell_start,
+                         const double4* pos, double* vel, void* frc, int32_t stride, double dt,
+                         double* part, DevState* st, const FuseOut& fo);
+// list-free cell path, any density and row tile (force_cells.hip)
 int32_t cells_homes_per_block();
 // rc2_form: fma_pair_form of the squared force cutoffs.
 void launch_force_cells(hipStream_t s, int32_t mixed, int32_t mode, int32_t rc2_form,
