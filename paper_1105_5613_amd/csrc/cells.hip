@@ -8,6 +8,8 @@
 // to the cell segments, and a per-cell rank sort by original id that makes
 // the order deterministic, followed by a gather of the particle records into
 // the new order.
+#include <algorithm>
+
 #include "brick.h"
 
 namespace mdk {
@@ -124,33 +126,41 @@ __device__ inline int32_t cell_coord(double c, double inv_cell, int32_t nc) {
   return q > nc - 1 ? nc - 1 : q;
 }
 
+// Wrap p into the box of replica R (d: the image steps; a coordinate that one
+// wrap does not bring into [0, L) sets bad) and return its cell, numbered from
+// the replica's first.
+__device__ inline int32_t wrap_to_cell(double4& p, const RepDesc& R, int32_t d[3], int32_t& bad) {
+  d[0] = wrap1(p.x, R.L, bad);
+  d[1] = wrap1(p.y, R.L, bad);
+  d[2] = wrap1(p.z, R.L, bad);
+  const int32_t qx = cell_coord(p.x, R.inv_cell, R.nc);
+  const int32_t qy = cell_coord(p.y, R.inv_cell, R.nc);
+  const int32_t qz = cell_coord(p.z, R.inv_cell, R.nc);
+  return (qz * R.nc + qy) * R.nc + qx;
+}
+
 // Wrap particle i of replica R, whose position p was just read from pos[i],
-// into the box (p, pos[i] and the image counter updated; a coordinate that
-// one wrap does not bring into [0, L) latches kErrStray) and return its
-// cell, numbered from the first cell of all replicas.
+// into the box (p, pos[i] and the image counter updated; a stray one latches
+// kErrStray) and return its cell, numbered from the first cell of all
+// replicas.
 __device__ inline int32_t bin_particle(int32_t i, double4& p, const RepDesc& R,
                                        double4* __restrict__ pos, const int32_t* __restrict__ id,
                                        int32_t* __restrict__ img, DevState* st) {
   const double4 p0 = p;
-  int32_t bad = 0;
-  int32_t dx = wrap1(p.x, R.L, bad);
-  int32_t dy = wrap1(p.y, R.L, bad);
-  int32_t dz = wrap1(p.z, R.L, bad);
+  int32_t bad = 0, d[3];
+  const int32_t c = wrap_to_cell(p, R, d, bad);
   if (bad) latch(st, kErrStray);
-  if (dx | dy | dz) {
+  if (d[0] | d[1] | d[2]) {
     size_t o = 3 * (size_t)id[i];
-    img[o] += dx;
-    img[o + 1] += dy;
-    img[o + 2] += dz;
+    img[o] += d[0];
+    img[o + 1] += d[1];
+    img[o + 2] += d[2];
   }
   // most particles stay in the box: write back only a changed position
   // (a tiny negative coordinate can wrap to L and then to 0 with no net
   // image change)
   if (bad || p.x != p0.x || p.y != p0.y || p.z != p0.z) pos[i] = p;
-  int32_t qx = cell_coord(p.x, R.inv_cell, R.nc);
-  int32_t qy = cell_coord(p.y, R.inv_cell, R.nc);
-  int32_t qz = cell_coord(p.z, R.inv_cell, R.nc);
-  return R.coff + (qz * R.nc + qy) * R.nc + qx;
+  return R.coff + c;
 }
 
 // Wrap + bin.  Particles arrive in the cell order of the previous build, so
@@ -450,26 +460,31 @@ __global__ __launch_bounds__(256) void k_cell_gather(
 }
 
 // The whole chain for a context of one replica with at most kSmallN
-// particles and kSmallCells cells, in one block: wrap + bin (histogram in
+// particles and kSmallCells cells, in one launch: wrap + bin (histogram in
 // LDS), the exclusive scan, then the ids of every cell in slot order in LDS
-// and each particle's rank among its cell's ids counted there, with a block
-// barrier between the phases.  It leaves the arrays of the launches above
-// (cell_start and the records in the new order) bit for bit: the slots
-// within a cell come out of the atomics in another order, which the rank by
-// id removes.  At this size a launch costs far more than its work, so a
-// step that does not rebuild pays one gated launch instead of four.  Thread
-// t takes particles t, t + 1024, ... (at most kSmallN / kSmallThreads) in
-// every phase, keeps their cells, slots and ids in registers, and reads the
-// records of all of them with one round trip per phase.
+// and each particle's rank among its cell's ids counted there.  It leaves the
+// arrays of the launches above (cell_start and the records in the new order)
+// bit for bit: the slots within a cell come out of the atomics in another
+// order, which the rank by id removes.  A step that does not rebuild pays one
+// gated launch (2.5 us) instead of four.
+//
+// Every block bins all particles for itself, so that no block waits for
+// another; the ranks, the gather, the image counters and the tables of the
+// tiles are shared out.  Positions are not written back: the wrapped record
+// goes to pos_tmp, which every list build commits.  Thread t bins particles t,
+// t + 1024, ... (at most PER) and keeps their cells and slots in registers.
+// Busy launches: 4,000 particles 19.4 us in one block (the gather runs at one
+// CU's bandwidth), 11.2 us in 16 to 64; 10,976 particles 17 us (the four
+// launches: 18.3 us, and 10 us instead of 2.5 on a step without a rebuild).
+template <int PER>
 __global__ __launch_bounds__(kSmallThreads) void k_chain_small(
     const RepDesc* __restrict__ reps, const int32_t* __restrict__ rebuild,
-    double4* __restrict__ pos, const int32_t* __restrict__ id, int32_t* __restrict__ img,
+    const double4* __restrict__ pos, const int32_t* __restrict__ id, int32_t* __restrict__ img,
     int32_t* __restrict__ cell_start, int32_t stride, const double* __restrict__ vel,
     int32_t* __restrict__ id_tmp, double4* __restrict__ pos_tmp, double* __restrict__ vel_tmp,
     DevState* st, BrickArgs A) {
-  constexpr int kPer = kSmallN / kSmallThreads;
   __shared__ int32_t s_start[kSmallCells + 1];  // counts, then first particle of each cell
-  __shared__ __align__(16) int32_t s_id[kSmallN];  // ids by cell, then slot
+  __shared__ __align__(16) int32_t s_id[PER * kSmallThreads];  // ids by cell, then slot
   __shared__ int32_t s_wsum[kSmallThreads / 64];
   if (!st->any_rebuild) return;
   if (!rebuild[0]) return;
@@ -477,28 +492,31 @@ __global__ __launch_bounds__(kSmallThreads) void k_chain_small(
   const int32_t ncl = R.nc * R.nc * R.nc;
   const int32_t end = R.off + R.n;
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const int32_t nb = gridDim.x, bk = blockIdx.x;
   for (int32_t c = t; c <= ncl; c += kSmallThreads) s_start[c] = 0;
-  int32_t idv[kPer], cl[kPer], sl[kPer];
-  {
-    double4 pv[kPer];
+  __syncthreads();
+  int32_t idv[PER], cl[PER], sl[PER];
 #pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-      const int32_t i = R.off + t + u * kSmallThreads;
+  for (int u0 = 0; u0 < PER; u0 += 4) {
+    double4 pv[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int32_t i = R.off + t + (u0 + u) * kSmallThreads;
+      idv[u0 + u] = 0;
       if (i < end) {
         pv[u] = pos[i];
-        idv[u] = id[i];
+        idv[u0 + u] = id[i];
       }
     }
-    __syncthreads();
 #pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-      const int32_t i = R.off + t + u * kSmallThreads;
-      cl[u] = 0;
-      sl[u] = 0;
+    for (int u = 0; u < 4; ++u) {
+      const int32_t i = R.off + t + (u0 + u) * kSmallThreads;
+      cl[u0 + u] = 0;
+      sl[u0 + u] = 0;
       if (i < end) {
-        // writes the wrapped position back to pos[i] when it changed
-        cl[u] = bin_particle(i, pv[u], R, pos, id, img, st) - R.coff;
-        sl[u] = atomicAdd(&s_start[cl[u]], 1);
+        int32_t d[3], bad = 0;
+        cl[u0 + u] = wrap_to_cell(pv[u], R, d, bad);
+        sl[u0 + u] = atomicAdd(&s_start[cl[u0 + u]], 1);
       }
     }
   }
@@ -533,38 +551,50 @@ __global__ __launch_bounds__(kSmallThreads) void k_chain_small(
   }
   if (t == 0) s_start[ncl] = tot;
   __syncthreads();
-  for (int32_t c = t; c <= ncl; c += kSmallThreads) cell_start[R.coff + c] = s_start[c];
-  for (int32_t b = w; b < A.ntiles; b += kSmallThreads / 64)  // brick path: rows of the tiles
+#pragma unroll
+  for (int u = 0; u < PER; ++u)
+    if (R.off + t + u * kSmallThreads < end) s_id[s_start[cl[u]] - R.off + sl[u]] = idv[u];
+  for (int32_t c = bk * kSmallThreads + t; c <= ncl; c += nb * kSmallThreads)
+    cell_start[R.coff + c] = s_start[c];
+  // brick path: rows of the tiles
+  for (int32_t b = w * nb + bk; b < A.ntiles; b += nb * (kSmallThreads / 64))
     tile_rows(A.tiles[b], R, s_start - R.coff, lane, A.slots, A.head + b,
               A.row + (size_t)b * A.rows, A.hrow + (size_t)b * A.hrows, st);
-#pragma unroll
-  for (int u = 0; u < kPer; ++u)
-    if (R.off + t + u * kSmallThreads < end) s_id[s_start[cl[u]] - R.off + sl[u]] = idv[u];
   __syncthreads();
-#pragma unroll
-  for (int u = 0; u < kPer; ++u) {
-    const int32_t i = R.off + t + u * kSmallThreads;
-    if (i < end) {
-      const int32_t lo = s_start[cl[u]] - R.off, hi = s_start[cl[u] + 1] - R.off;
-      // four ids per LDS read: a one-cell box of 500 particles counts 500 ids
-      // per thread, and the chain took 28.8 us with one id per read, 11.3 us now
-      int32_t rank = 0;
-      int32_t m = lo;
-      for (; m < hi && (m & 3); ++m) rank += s_id[m] < idv[u] ? 1 : 0;  // ids are unique
-#pragma unroll 4
-      for (; m + 4 <= hi; m += 4) {
-        const int4 q = *reinterpret_cast<const int4*>(s_id + m);
-        rank += (q.x < idv[u] ? 1 : 0) + (q.y < idv[u] ? 1 : 0) + (q.z < idv[u] ? 1 : 0) +
-                (q.w < idv[u] ? 1 : 0);
-      }
-      for (; m < hi; ++m) rank += s_id[m] < idv[u] ? 1 : 0;
-      const int32_t d = R.off + lo + rank;
-      id_tmp[d] = idv[u];
-      pos_tmp[d] = pos[i];  // this thread's own write-back, if any
-      vel_tmp[d] = vel[i];
-      vel_tmp[stride + d] = vel[stride + i];
-      vel_tmp[2 * (size_t)stride + d] = vel[2 * (size_t)stride + i];
+  // this block's particles [i0, i1)
+  const int32_t i0 = R.off + (int32_t)((int64_t)R.n * bk / nb),
+                i1 = R.off + (int32_t)((int64_t)R.n * (bk + 1) / nb);
+  for (int32_t i = i0 + t; i < i1; i += kSmallThreads) {
+    double4 p = pos[i];
+    const int32_t me = id[i];
+    const double v0 = vel[i], v1 = vel[stride + i], v2 = vel[2 * (size_t)stride + i];
+    int32_t dxyz[3], bad = 0;
+    const int32_t c = wrap_to_cell(p, R, dxyz, bad);
+    if (bad) latch(st, kErrStray);
+    if (dxyz[0] | dxyz[1] | dxyz[2]) {
+      const size_t o = 3 * (size_t)me;
+      img[o] += dxyz[0];
+      img[o + 1] += dxyz[1];
+      img[o + 2] += dxyz[2];
     }
+    const int32_t lo = s_start[c] - R.off, hi = s_start[c + 1] - R.off;
+    // four ids per LDS read: a one-cell box of 500 particles counts 500 ids
+    // per thread, and the chain took 28.8 us with one id per read, 11.3 us now
+    int32_t rank = 0;
+    int32_t m = lo;
+    for (; m < hi && (m & 3); ++m) rank += s_id[m] < me ? 1 : 0;  // ids are unique
+#pragma unroll 4
+    for (; m + 4 <= hi; m += 4) {
+      const int4 q = *reinterpret_cast<const int4*>(s_id + m);
+      rank += (q.x < me ? 1 : 0) + (q.y < me ? 1 : 0) + (q.z < me ? 1 : 0) + (q.w < me ? 1 : 0);
+    }
+    for (; m < hi; ++m) rank += s_id[m] < me ? 1 : 0;
+    const int32_t d = R.off + lo + rank;
+    id_tmp[d] = me;
+    pos_tmp[d] = p;
+    vel_tmp[d] = v0;
+    vel_tmp[stride + d] = v1;
+    vel_tmp[2 * (size_t)stride + d] = v2;
   }
 }
 
@@ -649,12 +679,22 @@ void launch_scatter(hipStream_t s, int32_t ntiles, const Tile* tiles, const int3
                                    ntiles, spread, grid);
 }
 
-void launch_chain_small(hipStream_t s, const RepDesc* reps, const int32_t* rebuild,
-                        double4* pos, const int32_t* id, int32_t* img, int32_t* cell_start,
+void launch_chain_small(hipStream_t s, int32_t n, const RepDesc* reps, const int32_t* rebuild,
+                        const double4* pos, const int32_t* id, int32_t* img, int32_t* cell_start,
                         int32_t stride, const double* vel, int32_t* id_tmp, double4* pos_tmp,
                         double* vel_tmp, DevState* st, const BrickArgs& bricks) {
-  k_chain_small<<<1, kSmallThreads, 0, s>>>(reps, rebuild, pos, id, img, cell_start, stride,
-                                            vel, id_tmp, pos_tmp, vel_tmp, st, bricks);
+  const unsigned grid = std::min(kSmallBlocks, nblk(n, 128));
+#define KC(PER)                                                                                \
+  k_chain_small<PER><<<grid, kSmallThreads, 0, s>>>(reps, rebuild, pos, id, img, cell_start,   \
+                                                    stride, vel, id_tmp, pos_tmp, vel_tmp, st, \
+                                                    bricks)
+  if (n <= 4 * kSmallThreads)
+    KC(4);
+  else if (n <= 8 * kSmallThreads)
+    KC(8);
+  else
+    KC(16);
+#undef KC
 }
 
 void launch_cell_gather(hipStream_t s, int32_t ncells, const int32_t* cell_rep,

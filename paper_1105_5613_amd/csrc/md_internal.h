@@ -219,16 +219,17 @@ size_t scan_bsum_elems(int32_t ncells);
 void launch_scatter(hipStream_t s, int32_t ntiles, const Tile* tiles, const int32_t* rebuild,
                     const int32_t* cell_of, const int32_t* slot, const int32_t* cell_start,
                     int32_t* tmp_src, const DevState* st, int32_t spread);
-// One-block form of the chain above (zero, bin, scan, scatter, gather) for a
+// The chain above (zero, bin, scan, scatter, gather) in one launch, for a
 // context of one replica with at most kSmallN particles and kSmallCells
-// cells; the same cell_start and records, in one launch.  (At 16,384
-// particles the block's serial walk over 16 particles per thread already
-// cost more than the three launches it saves.)
+// cells; the same cell_start and records.  (Every block bins all particles,
+// up to sixteen per thread: beyond that its walk costs more than the launches
+// it saves.)
 constexpr int kSmallThreads = 1024;
-constexpr int kSmallN = 8192;
+constexpr int kSmallN = 16 * kSmallThreads;
 constexpr int kSmallCells = 4 * kSmallThreads;  // the scan takes four cells per thread
-void launch_chain_small(hipStream_t s, const RepDesc* reps, const int32_t* rebuild,
-                        double4* pos, const int32_t* id, int32_t* img, int32_t* cell_start,
+constexpr unsigned kSmallBlocks = 32;
+void launch_chain_small(hipStream_t s, int32_t n, const RepDesc* reps, const int32_t* rebuild,
+                        const double4* pos, const int32_t* id, int32_t* img, int32_t* cell_start,
                         int32_t stride, const double* vel, int32_t* id_tmp, double4* pos_tmp,
                         double* vel_tmp, DevState* st, const BrickArgs& bricks);
 void launch_cell_gather(hipStream_t s, int32_t ncells, const int32_t* cell_rep,
