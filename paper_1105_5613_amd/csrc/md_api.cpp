@@ -407,7 +407,11 @@ BrickPair brick_pair(const md_params& p, const PairTab& t) {
 // fits the slots with 12 % to spare and whose homes fit one or two rounds of
 // a block (240), as the copy to LDS is paid per neighbourhood cell.  (Cells
 // between 2.8 and 3 wide hold 26 to 32 particles: 2 x 2 x 2 of them need up to
-// 2,350 slots, hence the larger LDS layout.)  The rule
+// 2,350 slots, hence the larger LDS layout.)  The smaller layout, of which
+// three blocks fit a CU, is taken where it holds eight home cells: nine in the
+// larger one (16,777,216 particles, 26.4 per cell) took 2,855 us per mixed
+// launch, eight here 2,545; with six or seven the larger one is the faster (262,144
+// particles, 28.3 per cell: 103 us a step, six cells in the smaller 120).  The rule
 // looks at the density of one replica only, so that a replica's sums are the
 // same alone and in a batch.
 bool plan_bricks(md_ctx c) {
@@ -448,15 +452,20 @@ bool plan_bricks(md_ctx c) {
     const double ppc = (double)d.n / ((double)nc * nc * nc);
     auto per = [&](int t) { return (int64_t)(nc + t - 1) / t; };
     int bx = 1, by = 1, bz = 1;
-    for (int x = 1; x <= std::min(4, nc); ++x)
-      for (int y = 1; y <= x; ++y)
-        for (int z = 1; z <= y; ++z) {
-          const double homes = ppc * x * y * z;
-          if (homes > 240.0 || slots(ppc, x, y, z) >= most) continue;
-          const int v = x * y * z, bv = bx * by * bz;
-          const int h = (x + 2) * (y + 2) * (z + 2), bh = (bx + 2) * (by + 2) * (bz + 2);
-          if (v > bv || (v == bv && h < bh)) bx = x, by = y, bz = z;
-        }
+    auto fits = [&](int32_t room) {
+      bx = by = bz = 1;
+      for (int x = 1; x <= std::min(4, nc); ++x)
+        for (int y = 1; y <= x; ++y)
+          for (int z = 1; z <= y; ++z) {
+            const double homes = ppc * x * y * z;
+            if (homes > 240.0 || slots(ppc, x, y, z) >= room) continue;
+            const int v = x * y * z, bv = bx * by * bz;
+            const int h = (x + 2) * (y + 2) * (z + 2), bh = (bx + 2) * (by + 2) * (bz + 2);
+            if (v > bv || (v == bv && h < bh)) bx = x, by = y, bz = z;
+          }
+      return bx * by * bz;
+    };
+    if (fits(std::min(most, kBrickSlots)) < 8) fits(most);
     const bool rbig = slots(ppc, bx, by, bz) >= kBrickSlots;
     const int32_t pass = nlist_brick_pass(rbig);
     big |= rbig;
