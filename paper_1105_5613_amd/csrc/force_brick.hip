@@ -87,6 +87,7 @@ __attribute__((amdgpu_waves_per_eu(EN || BIG || (!MIXED && TPP == 2) ? 4 : 6))) 
   __shared__ typename std::conditional<EN, EnergyTab<T>, char>::type s_en[1];
   __shared__ PairRow s_pair[NS > 2 ? 16 : 1];
   __shared__ double s_mass[4], s_im[4];
+  const bool halt = halted(st);  // read beside the tile tables
   const int32_t lb = xcd_block(blockIdx.x, gridDim.x);
   const int32_t tb = lb / A.split, share = lb % A.split;
   const TileRow* trow = A.row + (size_t)tb * A.rows;
@@ -130,7 +131,7 @@ __attribute__((amdgpu_waves_per_eu(EN || BIG || (!MIXED && TPP == 2) ? 4 : 6))) 
     while (r + 1 < nhr && s_home[r + 1].h <= h) ++r;
     return s_home[r].g + (h - s_home[r].h);
   };
-  if (halted(st)) {
+  if (halt) {
     // a list build queued before this launch overflowed (see kHalt): the
     // step is not taken, and a fused launch hands the positions unchanged to
     // the buffer the host swaps in

@@ -29,30 +29,45 @@ __global__ __launch_bounds__(kTile) void k_kick_drift(
     double* __restrict__ dmax, DevState* st, int32_t* __restrict__ counts, int32_t nzero) {
   __shared__ double s_im[4];
   __shared__ double s_red[kTile / 64];
-  if (halted(st)) return;  // an overflowed list build halts the queued steps
-  if (threadIdx.x < 4) s_im[threadIdx.x] = tab->inv_mass[threadIdx.x];
-  __syncthreads();
+  // the flag, the tile and its records in one round trip each, not four
+  const bool halt = halted(st);
   const int32_t tb = xcd_block(blockIdx.x, gridDim.x);
+  const Tile t = tiles[tb];
+  if (threadIdx.x < 4) s_im[threadIdx.x] = tab->inv_mass[threadIdx.x];
+  if (halt) return;  // an overflowed list build halts the queued steps
+  const int32_t i = t.start + threadIdx.x;
+  double4 p{};
+  double v0 = 0.0, v1 = 0.0, v2 = 0.0, f0 = 0.0, f1 = 0.0, f2 = 0.0, x0 = 0.0, x1 = 0.0, x2 = 0.0;
+  double l = 1.0;
+  if (i < t.end) {
+    p = pos[i];
+    v0 = vel[i];
+    v1 = vel[stride + i];
+    v2 = vel[2 * (size_t)stride + i];
+    f0 = (double)frc[i];
+    f1 = (double)frc[stride + i];
+    f2 = (double)frc[2 * (size_t)stride + i];
+    x0 = xref[i];
+    x1 = xref[stride + i];
+    x2 = xref[2 * (size_t)stride + i];
+    if (THERMO) l = lam[t.rep];
+  }
+  __syncthreads();
   // one replica: the cell histogram is only read inside a rebuild, so it is
   // cleared here every step instead of by a separate gated launch
   const int32_t gz = blockIdx.x * kTile + threadIdx.x;
   if (gz < nzero) counts[gz] = 0;
-  const Tile t = tiles[tb];
-  const int32_t i = t.start + threadIdx.x;
   double d2 = 0.0;
   if (i < t.end) {
-    double4 p = pos[i];
     const double hm = 0.5 * dt * s_im[(int32_t)p.w];
-    double v0 = vel[i], v1 = vel[stride + i], v2 = vel[2 * (size_t)stride + i];
     if (THERMO) {
-      const double l = lam[t.rep];
       v0 *= l;
       v1 *= l;
       v2 *= l;
     }
-    v0 += hm * (double)frc[i];
-    v1 += hm * (double)frc[stride + i];
-    v2 += hm * (double)frc[2 * (size_t)stride + i];
+    v0 += hm * f0;
+    v1 += hm * f1;
+    v2 += hm * f2;
     p.x += dt * v0;
     p.y += dt * v1;
     p.z += dt * v2;
@@ -64,8 +79,7 @@ __global__ __launch_bounds__(kTile) void k_kick_drift(
     vel[i] = v0;
     vel[stride + i] = v1;
     vel[2 * (size_t)stride + i] = v2;
-    const double e0 = p.x - xref[i], e1 = p.y - xref[stride + i],
-                 e2 = p.z - xref[2 * (size_t)stride + i];
+    const double e0 = p.x - x0, e1 = p.y - x1, e2 = p.z - x2;
     d2 = e0 * e0 + e1 * e1 + e2 * e2;
   }
 #pragma unroll
@@ -107,7 +121,7 @@ __global__ __launch_bounds__(kRedThreads) void k_reduce(const RepDesc* __restric
                                                         int32_t* __restrict__ rebuild,
                                                         md_obs* __restrict__ obs, DevState* st) {
   __shared__ double red[5][kRedThreads / 64];
-  if (halted(st)) return;  // the step was not taken (kHalt)
+  const bool halt = halted(st);  // read beside the replica's record
   const int32_t r = blockIdx.x;
   const RepDesc R = reps[r];
   // thread 0's per-replica inputs, fetched before the sums so that their
@@ -150,6 +164,7 @@ __global__ __launch_bounds__(kRedThreads) void k_reduce(const RepDesc* __restric
       for (int32_t b = R.tile0 + threadIdx.x; b < R.tile1; b += kRedThreads)
         m = fmax(m, dmax[b]);
   }
+  if (halt) return;  // the step was not taken (kHalt)
   // each wave's totals by a butterfly over its lanes, then the wave totals
   // in wave order by thread 0: a fixed order, one barrier
   double v[5] = {s[0] + c[0], s[1] + c[1], s[2] + c[2], m, mn};
