@@ -450,7 +450,6 @@ bool plan_bricks(md_ctx c) {
     RepDesc& d = c->reps_h[r];
     const int32_t nc = d.nc;
     const double ppc = (double)d.n / ((double)nc * nc * nc);
-    auto per = [&](int t) { return (int64_t)(nc + t - 1) / t; };
     int bx = 1, by = 1, bz = 1;
     auto fits = [&](int32_t room) {
       bx = by = bz = 1;
@@ -486,48 +485,63 @@ bool plan_bricks(md_ctx c) {
                             (int32_t)std::ceil(1.15 * ppc * hx * hy * hz / 32.0));
     c->brick_extra = std::max(c->brick_extra, (int32_t)(1.15 * cand / (64 * pass)));
     d.fb0 = c->brick_parts;
-    auto cut = [](int32_t n, int32_t parts, int32_t k) {
-      return (int32_t)((int64_t)n * k / parts);
+    // the tiles along each axis, as even as they come, and their bricks
+    struct Piece {
+      int32_t first, cells;
     };
-    const int32_t ntx = (int32_t)per(bx), nty = (int32_t)per(by), ntz = (int32_t)per(bz);
-    const int32_t units = !cells && (int64_t)ntx * nty * ntz <= 256 ? kTileUnits : 1;
-    for (int32_t z = 0; z < ntz; ++z)
-      for (int32_t y = 0; y < nty; ++y)
-        for (int32_t x = 0; x < ntx; ++x) {
+    auto cut = [](int32_t n, int32_t most_cells) {
+      const int32_t parts = (n + most_cells - 1) / most_cells;
+      std::vector<Piece> v(parts);
+      for (int32_t k = 0; k < parts; ++k) {
+        v[k].first = (int32_t)((int64_t)n * k / parts);
+        v[k].cells = (int32_t)((int64_t)n * (k + 1) / parts) - v[k].first;
+      }
+      return v;
+    };
+    const std::vector<Piece> tx = cut(nc, bx), ty = cut(nc, by), tz = cut(nc, bz);
+    std::vector<Piece> cx[5], cy[5], cz[5];  // bricks of a tile of that many cells
+    for (int32_t t = 1; t <= 4; ++t) cx[t] = cut(t, hx), cy[t] = cut(t, hy), cz[t] = cut(t, hz);
+    const int32_t units =
+        !cells && (int64_t)tx.size() * ty.size() * tz.size() <= 256 ? kTileUnits : 1;
+    c->btiles_h.reserve(c->btiles_h.size() + tx.size() * ty.size() * tz.size());
+    c->bricks_h.reserve(c->bricks_h.size() +
+                        (size_t)(1.3 * nc * nc * nc / (hx * hy * hz)) + 64);
+    for (const Piece& z : tz)
+      for (const Piece& y : ty)
+        for (const Piece& x : tx) {
           BrickTile t{};
           t.rep = r;
-          t.cx = cut(nc, ntx, x);
-          t.cy = cut(nc, nty, y);
-          t.cz = cut(nc, ntz, z);
-          t.tx = cut(nc, ntx, x + 1) - t.cx;
-          t.ty = cut(nc, nty, y + 1) - t.cy;
-          t.tz = cut(nc, ntz, z + 1) - t.cz;
+          t.cx = x.first;
+          t.cy = y.first;
+          t.cz = z.first;
+          t.tx = x.cells;
+          t.ty = y.cells;
+          t.tz = z.cells;
           t.units = units;
           t.part = c->brick_parts;
           c->brick_parts += units;
           const int32_t id = (int32_t)c->btiles_h.size();
+          t.b0 = (int32_t)c->bricks_h.size();
+          for (const Piece& w : cz[t.tz])
+            for (const Piece& v : cy[t.ty])
+              for (const Piece& u : cx[t.tx]) {
+                Brick b{};
+                b.tile = id;
+                b.pass = (int8_t)pass;
+                b.lx = (int8_t)u.first;
+                b.ly = (int8_t)v.first;
+                b.lz = (int8_t)w.first;
+                b.hx = (int8_t)u.cells;
+                b.hy = (int8_t)v.cells;
+                b.hz = (int8_t)w.cells;
+                c->bricks_h.push_back(b);
+              }
+          t.nb = (int32_t)c->bricks_h.size() - t.b0;
+          bricks = std::max(bricks, t.nb);
           c->btiles_h.push_back(t);
           c->ba.rows = std::max(c->ba.rows, (t.ty + 2) * (t.tz + 2));
           c->ba.hrows = std::max(c->ba.hrows, t.ty * t.tz);
           c->brick_homes = std::max(c->brick_homes, ppc * t.tx * t.ty * t.tz);
-          auto n = [](int32_t t, int32_t h) { return (t + h - 1) / h; };
-          const int32_t ax = n(t.tx, hx), ay = n(t.ty, hy), az = n(t.tz, hz);
-          c->btiles_h[id].b0 = (int32_t)c->bricks_h.size();
-          c->btiles_h[id].nb = ax * ay * az;
-          bricks = std::max(bricks, ax * ay * az);
-          for (int32_t k = 0; k < ax * ay * az; ++k) {
-            const int32_t ix = k % ax, iy = k / ax % ay, iz = k / (ax * ay);
-            Brick b{};
-            b.tile = id;
-            b.pass = (int8_t)pass;
-            b.lx = (int8_t)cut(t.tx, ax, ix);
-            b.ly = (int8_t)cut(t.ty, ay, iy);
-            b.lz = (int8_t)cut(t.tz, az, iz);
-            b.hx = (int8_t)(cut(t.tx, ax, ix + 1) - b.lx);
-            b.hy = (int8_t)(cut(t.ty, ay, iy + 1) - b.ly);
-            b.hz = (int8_t)(cut(t.tz, az, iz + 1) - b.lz);
-            c->bricks_h.push_back(b);
-          }
         }
     d.fb1 = c->brick_parts;
   }
