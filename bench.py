@@ -37,10 +37,10 @@ import time
 ROOT = os.path.dirname(os.path.abspath(__file__))
 METRIC = "particle-steps/sec on 1 MI355X + % HBM roofline; mixed/batched vs plain FP64"
 HBM_PEAK_GBS = 8000.0
-FORCE_SRC = os.path.join(ROOT, "paper_1105_5613_amd", "csrc", "force.hip")
-# the list build fixes the order in which the force kernel gathers, and so
-# its traffic: the counters hold for this pair of sources only
-LIST_SRC = os.path.join(ROOT, "paper_1105_5613_amd", "csrc", "nlist.hip")
+FORCE_SRC = os.path.join(ROOT, "paper_1105_5613_amd", "csrc", "force_brick.hip")
+# the list build fixes the entries that the force kernel streams, and so its
+# traffic: the counters hold for this pair of sources only
+LIST_SRC = os.path.join(ROOT, "paper_1105_5613_amd", "csrc", "nlist_brick.hip")
 COUNTERS_JSON = os.path.join(ROOT, "profiles", "force_counters.json")
 FP64_OPS_JSON = os.path.join(ROOT, "profiles", "fp64_ops.json")
 FP64_PEAK_TFLOPS = 78.6
@@ -58,7 +58,7 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-def force_bytes_per_particle(nbar: float, mixed: bool) -> float:
+def force_bytes_per_particle(nbar: float, mixed: bool, tiles: bool = False) -> float:
     """Algorithmic HBM bytes per particle of one in-step force launch of an
     NVE step, which also applies the next step's half kick and drift.
 
@@ -70,16 +70,24 @@ def force_bytes_per_particle(nbar: float, mixed: bool) -> float:
     moves: the stored position record is 32 bytes (species kept as a
     double), and its 4 padding bytes per read and 8 per write are not
     counted.
+
+    tiles: the default path of the Lennard-Jones boxes, whose lists hold
+    16-bit entries (2 nbar) and whose partners come from LDS, so that mixed
+    has no record of its own.
     """
+    if tiles:
+        return 4 + 2 * nbar + 28 + 48 + 24 + 24
     return 4 + 4 * nbar + 28 + 48 + 24 + 24 + (32 if mixed else 0)
 
 
-def step_bytes_per_particle(nbar: float, mixed: bool, rebuilds_per_step: float) -> float:
+def step_bytes_per_particle(nbar: float, mixed: bool, rebuilds_per_step: float,
+                            tiles: bool = False) -> float:
     """Algorithmic HBM bytes per particle-step of the whole step: the force
     launch (kick and drift included) and one rebuild (bin 28, sort keys 24,
-    reorder 160, list write 4 nbar + 4) times the measured rebuilds per step."""
-    rebuild = 28 + 24 + 160 + 4 * nbar + 4
-    return force_bytes_per_particle(nbar, mixed) + rebuild * rebuilds_per_step
+    reorder 160, list write 4 nbar + 4, with tiles 2 nbar + 4) times the
+    measured rebuilds per step."""
+    rebuild = 28 + 24 + 160 + (2 if tiles else 4) * nbar + 4
+    return force_bytes_per_particle(nbar, mixed, tiles) + rebuild * rebuilds_per_step
 
 
 def copy_gbs(torch) -> float:
@@ -169,7 +177,7 @@ def floored_force_error(F_sel, Fo_sel, frms: float) -> float:
     return float(np.max(d / np.maximum(np.linalg.norm(Fo_sel, axis=1), frms)))
 
 
-def run_drift(precision: int, inputs, path: int = 1, potential: int = 0, global_rc=None,
+def run_drift(precision: int, inputs, path: int = 0, potential: int = 0, global_rc=None,
               dt: float = 0.005, steps: int = DRIFT_STEPS):
     """D over `steps` (default DRIFT_STEPS) NVE steps of a fresh context from
     the form's initial state (energies every step), so the figure does not
@@ -191,7 +199,7 @@ def run_drift(precision: int, inputs, path: int = 1, potential: int = 0, global_
 
 
 def run_single(torch, precision: int, inputs, steps: int, warmup: int, prof_every: int,
-               path: int = 1, potential: int = 0, global_rc=None, dt: float = 0.005, T0=None,
+               path: int = 0, potential: int = 0, global_rc=None, dt: float = 0.005, T0=None,
                graph_steps: int = 0, sample_forces: bool = False):
     from paper_1105_5613_amd import System, make_params
     import initconf
@@ -260,8 +268,10 @@ def run_batched(torch, precision: int, systems, temps, steps: int, warmup: int,
     choice = None
     if tune:
         from paper_1105_5613_amd import tune as tuner
+        from paper_1105_5613_amd.md import MD_PATH_AUTO, MD_PATH_GATHER
         p, rep_ = tuner.autotune(p, n, L, x, v, t, T0=temps, steps=60, warmup=20,
-                                 skins=TUNE_SKINS, tile_cells=(0,), use_cache=False,
+                                 skins=TUNE_SKINS, paths=(MD_PATH_AUTO, MD_PATH_GATHER),
+                                 tile_cells=(0,), use_cache=False,
                                  cache_path=None)
         choice = {"choice": rep_.get("choice"),
                   "trials": [{**tr["choice"], "rate": round(tr["rate"], 1)}
@@ -352,7 +362,7 @@ def cpu_baseline(inputs, nsteps: int, nsteps_1t: int = 4):
 
 
 def cells_flops(n: int, force_ms: float):
-    """The list-free force kernel is bound by FP64 vector issue, not HBM: its
+    """The list-free force kernel of the row tiles is bound by FP64 vector issue, not HBM: its
     FP64 FLOP rate (committed operation counts per particle x n / the
     measured mean launch time) against the 78.6 TFLOP/s FP64 vector peak."""
     fpp = fp64_flops_per_particle("cells_fp64")
@@ -429,10 +439,10 @@ def counters_summary(args):
            "copy_bytes": COPY_BYTES, "copy_fetch_kib": cf, "copy_write_kib": cw,
            "copy_factor_fetch": copy_kib / cf, "copy_factor_write": copy_kib / cw,
            "forms": {}, "commands": args.commands}
-    runs = [("fp64", "k_force<false, 2", args.fetch_dir, args.write_dir),
-            ("mixed", "k_force<true, 2", args.fetch_dir, args.write_dir)]
+    runs = [("fp64", "<false, 2", args.fetch_dir, args.write_dir),
+            ("mixed", "<true, 2", args.fetch_dir, args.write_dir)]
     if args.large_fetch_dir and args.large_write_dir:
-        runs.append(("large_mixed", "k_force<true, 2", args.large_fetch_dir,
+        runs.append(("large_mixed", "<true, 2", args.large_fetch_dir,
                      args.large_write_dir))
     for form, key, fdir, wdir in runs:
         try:
@@ -532,7 +542,7 @@ def main():
 
     forms_out = {}
     for f, r in res.items():
-        b = force_bytes_per_particle(r["nbar"], f == "mixed")
+        b = force_bytes_per_particle(r["nbar"], f == "mixed", tiles=True)
         tr = counters_traffic(f)
         ach = gbs(n * b, r["force_ms_avg"])
         forms_out[f] = {"value": round(r["rate"], 1), "ms_per_step": round(r["ms_per_step"], 5),
@@ -544,7 +554,7 @@ def main():
                         "step_algorithmic_frac_hbm": round(
                             r["rate"] * step_bytes_per_particle(
                                 r["nbar"], f == "mixed",
-                                r["rebuilds"] / max(r["steps_total"], 1)) / 1e9 / HBM_PEAK_GBS, 4),
+                                r["rebuilds"] / max(r["steps_total"], 1), tiles=True) / 1e9 / HBM_PEAK_GBS, 4),
                         "mean_list_length": round(r["nbar"], 3), "rebuilds": r["rebuilds"],
                         "energy_drift_per_particle_per_1000_steps": (r["drift"] or {}).get("D"),
                         "energy_drift": r["drift"],
@@ -560,7 +570,7 @@ def main():
         log(f"  large mixed drift window: {DRIFT_STEPS} NVE steps")
         rl["drift"] = None if args.no_drift else run_drift(1, big)
         del big
-        bl = force_bytes_per_particle(rl["nbar"], True)
+        bl = force_bytes_per_particle(rl["nbar"], True, tiles=True)
         ach = gbs(nl * bl, rl["force_ms_avg"])
         trl = counters_traffic("large_mixed") if nl == LARGE_N else None
         log(f"  large mixed: {rl['rate']:.4e} particle-steps/s, {rl['ms_per_step']:.3f} ms/step, "
@@ -660,13 +670,13 @@ def main():
     head_mixed = "fp64" not in res
     roof = None
     if head is not None and head["force_ms_avg"]:
-        bpp = force_bytes_per_particle(head["nbar"], head_mixed)
+        bpp = force_bytes_per_particle(head["nbar"], head_mixed, tiles=True)
         achieved = gbs(n * bpp, head["force_ms_avg"])
         traffic = counters_traffic("mixed" if head_mixed else "fp64")
         roof = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                 "traffic": None if traffic is None else round(traffic),
-                "kernel": "k_force (pair forces, second half kick, next step's half kick, "
+                "kernel": "k_force_brick (pair forces, second half kick, next step's half kick, "
                           "drift and skin check)",
                 "algorithmic_bytes_per_launch": round(n * bpp),
                 "force_ms_avg": round(head["force_ms_avg"], 5)}

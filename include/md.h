@@ -76,7 +76,15 @@ enum { MD_FP64 = 0, MD_MIXED = 1 };
  * method", Fig. 1): no neighbour list at all, every force launch searches
  * the 27-cell stencil of each particle (cells rebuilt by the skin rule);
  * needs >= 3 cells per box side; md_get_neighbors and md_list_stats return
- * MD_ESTATE.  AUTO is GATHER. */
+ * MD_ESTATE.  AUTO takes tiles of cells where every replica has at
+ * least 3 cells per side, an expected list of at least 48 entries and 27 cells
+ * that fit a block's LDS, and tpp and unroll are 0: a block copies a tile's
+ * neighbourhood into LDS and walks 16-bit list entries against it, and the
+ * list search is a matrix product with an exact FP64 test of the pairs near
+ * the cutoff.  The partners, and so md_get_neighbors, are GATHER's; a box that
+ * condenses beyond the LDS goes on with gather lists.  Elsewhere AUTO is
+ * GATHER.  CELLS runs on the same tiles with tile_cells = 0, by row tiles
+ * otherwise or in boxes too dense for them. */
 enum { MD_PATH_AUTO = 0, MD_PATH_GATHER = 1, MD_PATH_STAGED = 2, MD_PATH_CELLS = 3 };
 #define MD_MAXT 4
 
@@ -97,22 +105,26 @@ typedef struct {
   int32_t max_neighbors; /* neighbour capacity per particle; 0 = from density */
   int32_t graph_steps;   /* steps per captured hipGraph in md_step; 0 = direct */
   int32_t tpp;           /* lanes per particle in the force kernel (1,2,4,8; staged
-                            path 1,2,4); 0 = auto */
+                            path 1,2,4); 0 = auto.  With AUTO, a value other than 0
+                            here or in unroll names a gather variant */
   int32_t unroll;        /* list slots gathered per pipelined chunk in the force
                             kernel (1,2,4,8); 0 = auto */
   int32_t path;          /* MD_PATH_AUTO, MD_PATH_GATHER, MD_PATH_STAGED or MD_PATH_CELLS */
-  int32_t tile_cells;    /* staged path: cells per row tile (1..64); 0 = auto */
+  int32_t tile_cells;    /* staged path: cells per row tile (1..64); 0 = auto.  Cell
+                            path: 0 = tiles of cells where they fit, otherwise row
+                            tiles of that many cells */
   int32_t stage_slots;   /* staged path: LDS slots per tile (>= 64); slots beyond are
                             read from global memory; 0 = auto */
   int32_t split_kick;    /* 0 = auto: in directly launched NVE steps of a one-replica
-                            context on the gather path, the force launch of a step also
+                            context (AUTO, GATHER; CELLS on tiles of cells), the force
+                            launch of a step also
                             applies the next step's first half kick and drift (same
                             arithmetic and results, one pass over the particles fewer per
                             step; never on the last step of an md_step call, so the state
                             it leaves is complete); 1 = always a separate kick/drift
                             launch */
-  int32_t small_box;     /* 0 = auto: a context of one box of at most 8,192 particles
-                            (and 4,096 cells) rebuilds its cells in one block, and one of
+  int32_t small_box;     /* 0 = auto: a context of one box of at most 16,384 particles
+                            (and 4,096 cells) rebuilds its cells in one launch, and one of
                             at most 16,384 particles with >= 3 cells per side searches
                             its list (gather path) with 32 lanes per particle: the same
                             cells and lists bit for bit, with fewer launches and less

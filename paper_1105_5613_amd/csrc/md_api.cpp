@@ -317,8 +317,8 @@ int32_t brick_threads(md_ctx c) {
   return c->ba.ntiles * c->ba.split <= 256 ? kBrickThreads : std::max(256, std::min(want, 512));
 }
 
-// energy: form PE and W (the staged and list-free kernels always do).
-// mode 2 (gather path only): the fused NVE step, see FuseOut; the caller
+// energy: form PE and W (the row-tile kernels always do).
+// mode 2 (gather lists, tiles of cells): the fused NVE step, see FuseOut; the caller
 // swaps the position buffers after the launch.
 void launch_forces(md_ctx c, int32_t mode, hipStream_t s, int32_t energy = 1,
                    int32_t nzero = 0) {
@@ -770,8 +770,8 @@ void launch_forces0(md_ctx c) {
 }
 
 
-// Directly launched NVE steps of a one-replica gather-path context can fuse
-// the next step's kick and drift into the force launch (md_params.split_kick).
+// Directly launched NVE steps of a one-replica context on gather lists or tiles
+// of cells can fuse the next step's kick and drift into the force launch (md_params.split_kick).
 bool can_fuse(md_ctx c, int32_t thermo) {
   return !thermo && c->nrep == 1 && (!c->cells || c->search) && !c->staged && c->p.split_kick == 0;
 }

@@ -1,5 +1,6 @@
 """Autotuner for choices that need a fresh context: kernel path (gather or
-staged), list skin, staged tile length (cells per row tile).  Each candidate runs a short trial
+staged by default; pass MD_PATH_AUTO among the paths to try the tiles of
+cells, the fastest in most Lennard-Jones boxes), list skin, staged tile length (cells per row tile).  Each candidate runs a short trial
 from the caller's state in its own context (the caller's context is never
 touched); inside each trial md_autotune picks the force-kernel variant
 (lanes per particle, unroll).  The fastest candidate wins.
@@ -71,6 +72,9 @@ def autotune(params: md.Params, n, L, x, v, types, *, T0=None, steps: int = 60,
                     continue
                 for tc in tile_cells:
                     cands.append(dict(path=path, skin=float(skin), tile_cells=int(tc)))
+            elif path == md.MD_PATH_AUTO:
+                # a force variant named by tpp or unroll would be a gather one
+                cands.append(dict(path=path, skin=float(skin), tpp=0, unroll=0))
             else:
                 cands.append(dict(path=path, skin=float(skin)))
     trials = []
@@ -89,7 +93,7 @@ def autotune(params: md.Params, n, L, x, v, types, *, T0=None, steps: int = 60,
         torch.cuda.synchronize()
         wall = time.perf_counter() - t0
         s.close()
-        choice = dict(cand, tpp=t["tpp"], unroll=t["unroll"])
+        choice = dict(dict(tpp=t["tpp"], unroll=t["unroll"]), **cand)
         trials.append({"choice": choice, "rate": sum(n) * steps / wall,
                        "force_ms": t["force_ms"]})
     if not trials:
