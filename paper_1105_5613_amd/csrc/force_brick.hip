@@ -27,7 +27,7 @@
 // (BIG: contexts with wider cells take 3,072 slots, two blocks per CU.)
 // Tiles of 2 x 2 x 2 cells (213 homes, 1,709 slots at rho = 1.2) put three
 // blocks of eight waves on a CU (51 KB of LDS each).  Measured per launch at
-// 1,048,576 particles, gather -> brick: FP64 264 -> 201 us, mixed 193 -> 153 us.
+// 1,048,576 particles, gather -> brick: FP64 264 -> 198 us, mixed 193 -> 145 us.
 //
 // TPP lanes take one particle: of each 8-entry chunk lane p takes the entries
 // [8 p / TPP, 8 (p + 1) / TPP).  Sums are kept per pair of entries (0-1, 2-3,
@@ -63,10 +63,10 @@ __device__ inline double rsqrt3(double r2) {
   return __builtin_fma(y * e, __builtin_fma(e, 0.375, 0.5), y);
 }
 
-// Registers: three blocks of eight waves fit a CU at 80 VGPRs.  The FP64 form
-// with two lanes per particle spills there (235 us per NVE launch at
-// 1,048,576 particles) and runs two blocks without (211 us; four lanes at 80
-// VGPRs: 230 us); the mixed form is the other way round (160 against 183 us).
+// Registers: three blocks of eight waves fit a CU at 80 VGPRs, which the mixed
+// form holds without spills.  The FP64 form with two lanes per particle spills
+// there (203 us per NVE launch at 1,048,576 particles) and runs two blocks at
+// 96 without (198 us; four lanes at 80 VGPRs: 230 us).
 template <bool MIXED, int MODE, int TPP, bool EN, int NS, bool BIG>
 __global__ __launch_bounds__(kBrickThreads)
 __attribute__((amdgpu_waves_per_eu(EN || BIG || (!MIXED && TPP == 2) ? 4 : 6))) void k_force_brick(
@@ -356,13 +356,16 @@ __attribute__((amdgpu_waves_per_eu(EN || BIG || (!MIXED && TPP == 2) ? 4 : 6))) 
     for (int k = 0; k < kAhead; ++k) load(e[k]);
     for (int32_t c = 0; c < me.nch; ++c) {
       load(e[kAhead]);  // the chunks past a row's last one are allocated
-      double qx[E], qy[E], qz[E];
+      // two entries in flight: four held 24 registers and spilled at 80 in the
+      // mixed form (166 us per launch, 145 so; FP64 201, 198)
 #pragma unroll
-      for (int u = 0; u < E; ++u)
-        at((u & 1) ? e[0][u / 2] >> 16 : e[0][u / 2], qx[u], qy[u], qz[u]);
+      for (int k = 0; k < E / 2; ++k) {
+        double qx[2], qy[2], qz[2];
 #pragma unroll
-      for (int u = 0; u < E; ++u)
-        pair((u & 1) ? e[0][u / 2] >> 16 : e[0][u / 2], qx[u], qy[u], qz[u], u / 2);
+        for (int u = 0; u < 2; ++u) at(u ? e[0][k] >> 16 : e[0][k], qx[u], qy[u], qz[u]);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) pair(u ? e[0][k] >> 16 : e[0][k], qx[u], qy[u], qz[u], k);
+      }
 #pragma unroll
       for (int k = 0; k < kAhead; ++k)
 #pragma unroll
