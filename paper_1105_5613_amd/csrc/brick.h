@@ -146,6 +146,19 @@ __device__ inline void tile_rows(const BrickTile& T, const RepDesc& R, const int
   }
 }
 
+// Sorted index of home h of a tile with nh home particles, from its home rows;
+// places past the last home stand for the first one.  A tile without home
+// particles has none: its rows' starts may lie at the end of the particle
+// arrays, where nothing is to be read.
+__host__ __device__ inline int32_t home_index(const HomeRow* hr, int32_t nhr, int32_t h,
+                                              int32_t nh) {
+  if (nh <= 0) return -1;
+  if (h >= nh) h = 0;
+  int32_t r = 0;
+  while (r + 1 < nhr && hr[r + 1].h <= h) ++r;
+  return hr[r].g + (h - hr[r].h);
+}
+
 // brick tables of a context
 struct BrickArgs {
   int32_t ntiles, nbricks;

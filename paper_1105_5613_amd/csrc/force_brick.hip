@@ -126,11 +126,6 @@ __attribute__((amdgpu_waves_per_eu(EN || BIG || (!MIXED && TPP == 2) ? 4 : 6))) 
     s_z[kPadSlot] = 0.0;
   }
   __syncthreads();
-  auto home = [&](int32_t h) {
-    int r = 0;
-    while (r + 1 < nhr && s_home[r + 1].h <= h) ++r;
-    return s_home[r].g + (h - s_home[r].h);
-  };
   if (halt) {
     // a list build queued before this launch overflowed (see kHalt): the
     // step is not taken, and a fused launch hands the positions unchanged to
@@ -138,7 +133,7 @@ __attribute__((amdgpu_waves_per_eu(EN || BIG || (!MIXED && TPP == 2) ? 4 : 6))) 
     if (blockIdx.x == 0 && threadIdx.x == 0) st->any_rebuild = 0;
     if constexpr (MODE == 2) {
       for (int32_t h = h0 + threadIdx.x; h < nh; h += nthr) {
-        const int32_t i = home(h);
+        const int32_t i = home_index(s_home, nhr, h, nh);
         fo.pos_out[i] = pos[i];
       }
     }
@@ -159,9 +154,9 @@ __attribute__((amdgpu_waves_per_eu(EN || BIG || (!MIXED && TPP == 2) ? 4 : 6))) 
   };
   // the first round's home particle, in flight under the copy to LDS
   auto load_home = [&](int32_t h) {
-    Home m;
-    m.i = home(h < nh ? h : 0);
-    m.p = pos[m.i];
+    Home m{};
+    m.i = home_index(s_home, nhr, h, nh);
+    if (nh > 0) m.p = pos[m.i];
     m.nch = h < nh ? min(A.nchunk[m.i], A.capc) : 0;
     return m;
   };

@@ -125,9 +125,7 @@ k_force_search(BrickArgs A, const RepDesc* __restrict__ reps, const PairTab* __r
       const HomeRow* hr = A.hrow + (size_t)tb * A.hrows;
       const int32_t nh = A.head[tb].nh, nhr = Tl.ty * Tl.tz;
       for (int32_t h = threadIdx.x; h < nh; h += nthr) {
-        int r = 0;
-        while (r + 1 < nhr && hr[r + 1].h <= h) ++r;
-        const int32_t i = hr[r].g + (h - hr[r].h);
+        const int32_t i = home_index(hr, nhr, h, nh);
         fo.pos_out[i] = pos[i];
       }
     }

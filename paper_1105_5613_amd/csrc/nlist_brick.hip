@@ -531,9 +531,7 @@ __global__ __launch_bounds__(256) void k_decode_brick(BrickArgs A, int32_t cap,
   const TileRow* tr = A.row + (size_t)blockIdx.x * A.rows;
   const HomeRow* hr = A.hrow + (size_t)blockIdx.x * A.hrows;
   for (int32_t h = threadIdx.x; h < A.head[blockIdx.x].nh; h += blockDim.x) {
-    int r = 0;
-    while (r + 1 < nhr && hr[r + 1].h <= h) ++r;
-    const int32_t i = hr[r].g + (h - hr[r].h);
+    const int32_t i = home_index(hr, nhr, h, A.head[blockIdx.x].nh);
     const int32_t n = min(ncount[i], cap), nch = min(A.nchunk[i], A.capc);
     const uint16_t* e = reinterpret_cast<const uint16_t*>(A.list + list_base(i, A.capc));
     const size_t b = list_base(i, cap);
