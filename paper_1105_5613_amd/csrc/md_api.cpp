@@ -658,23 +658,43 @@ md_status upload_blocks(md_ctx c) {
   return MD_OK;
 }
 
+// The buffers of the gather path, all of them or none.
+md_status alloc_gather(md_ctx c) {
+  uint32_t* nbr = nullptr;
+  int4 *rec = nullptr, *alt = nullptr;
+  md_status rc = dalloc(c, &nbr, list_elems(c->ntot, c->cap));
+  if (!rc && c->mixed) rc = dalloc(c, &rec, (size_t)c->stride);
+  if (!rc && c->mixed) rc = dalloc(c, &alt, (size_t)c->stride);
+  if (rc) {
+    dfree(c, nbr);
+    dfree(c, rec);
+    return rc;
+  }
+  c->nbr = nbr;
+  c->pos16 = rec;
+  c->pos16_alt = alt;
+  return MD_OK;
+}
+
 // A tile whose neighbourhood outgrew the LDS slots (a box that condensed far
 // above its mean density): the context goes on with gather lists, which take
-// any density.  The caller rebuilds every replica.
+// any density.  The caller rebuilds every replica.  Nothing is switched before
+// the gather buffers are there: a call that fails here leaves the context on
+// its tiles, to try again at the next build.  (Where the two lists do not fit
+// side by side, the tiles' is given back first; build_all asks for it again.)
 md_status leave_brick(md_ctx c) {
   HIPCHECK(c, hipStreamSynchronize(c->stream));
+  md_status rc = alloc_gather(c);
   dfree(c, c->ba.list);
   c->ba.list = nullptr;
+  if (rc) rc = alloc_gather(c);
+  if (rc) {
+    c->built = c->forces_valid = false;
+    return rc;
+  }
   c->ba.ntiles = 0;
   c->ba.nbricks = 0;
   c->brick = false;
-  md_status rc = dalloc(c, &c->nbr, list_elems(c->ntot, c->cap));
-  if (!rc && c->mixed) rc = dalloc(c, &c->pos16, (size_t)c->stride);
-  if (!rc && c->mixed) rc = dalloc(c, &c->pos16_alt, (size_t)c->stride);
-  if (rc) {
-    c->built = false;
-    return rc;
-  }
   c->tpp = 2;
   c->unroll = 4;
   gather_blocks(c);
@@ -695,6 +715,10 @@ md_status leave_search(md_ctx c) {
 // Full rebuild of every replica (md_build_cells and the first build after
 // md_set_state); grows the neighbour capacity once on overflow.
 md_status build_all(md_ctx c) {
+  if (c->brick && !c->ba.list) {  // given back by a leave_brick that failed
+    const md_status rc = dalloc(c, &c->ba.list, chunk_elems(c->ntot, c->ba.capc));
+    if (rc) return rc;
+  }
   for (bool grown = false;;) {
     launch_mark_rebuild(c->stream, c->nrep, c->rebuild, c->st);
     run_chain(c, c->stream);
@@ -1429,6 +1453,8 @@ md_status md_step(md_ctx c, int32_t nsteps, const double* T0, const double* T1,
     if (rc) {
       c->built = false;
       c->forces_valid = false;
+      const DevState z{};  // reported by this call
+      HIPCHECK(c, hipMemcpy(c->st, &z, sizeof(DevState), hipMemcpyHostToDevice));
       return rc;
     }
     st.err = 0;
