@@ -140,8 +140,8 @@ __attribute__((amdgpu_waves_per_eu(EN || BIG || (!MIXED && TPP == 2) ? 4 : 6))) 
     return;
   }
   if constexpr (MODE == 2) {
-    const int32_t gz = blockIdx.x * nthr + threadIdx.x;
-    if (gz < fo.nzero) fo.counts[gz] = 0;
+    const uint32_t gz = blockIdx.x * (uint32_t)nthr + threadIdx.x;  // up to 2^32 (plan_bricks)
+    if (gz < (uint32_t)fo.nzero) fo.counts[gz] = 0;
   }
   const RepDesc& R = reps[Tl.rep];
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;

@@ -132,8 +132,8 @@ k_force_search(BrickArgs A, const RepDesc* __restrict__ reps, const PairTab* __r
     return;
   }
   if constexpr (MODE == 2) {
-    const int32_t gz = blockIdx.x * nthr + threadIdx.x;
-    if (gz < fo.nzero) fo.counts[gz] = 0;
+    const uint32_t gz = blockIdx.x * (uint32_t)nthr + threadIdx.x;  // up to 2^32 (plan_bricks)
+    if (gz < (uint32_t)fo.nzero) fo.counts[gz] = 0;
   }
   if ((int)threadIdx.x < nrow) s_row[threadIdx.x] = trow[threadIdx.x];
   for (int k = threadIdx.x; k < kPlanes * (kBrickSlots / 32 + 1); k += nthr) (&s_sp[0][0])[k] = 0u;

@@ -429,6 +429,32 @@ bool plan_bricks(md_ctx c) {
   auto slots = [&](double ppc, int x, int y, int z) {
     return spare * ppc * (x + 2) * (y + 2) * (z + 2) + 48.0;
   };
+  // cells per axis of a replica's tiles, and whether they take the larger layout
+  struct Shape {
+    int32_t x, y, z;
+    bool big;
+  };
+  auto shape = [&](const RepDesc& d) {
+    const double ppc = (double)d.n / ((double)d.nc * d.nc * d.nc);
+    Shape b{};
+    auto fits = [&](int32_t room) {
+      b.x = b.y = b.z = 1;
+      for (int x = 1; x <= std::min(4, d.nc); ++x)
+        for (int y = 1; y <= x; ++y)
+          for (int z = 1; z <= y; ++z) {
+            const double homes = ppc * x * y * z;
+            if (homes > 240.0 || slots(ppc, x, y, z) >= room) continue;
+            const int v = x * y * z, bv = b.x * b.y * b.z;
+            const int h = (x + 2) * (y + 2) * (z + 2), bh = (b.x + 2) * (b.y + 2) * (b.z + 2);
+            if (v > bv || (v == bv && h < bh)) b.x = x, b.y = y, b.z = z;
+          }
+      return b.x * b.y * b.z;
+    };
+    if (fits(std::min(most, kBrickSlots)) < 8) fits(most);
+    b.big = slots(ppc, b.x, b.y, b.z) >= kBrickSlots;
+    return b;
+  };
+  int64_t tiles = 0;
   for (const RepDesc& d : c->reps_h) {
     if (d.nc < 3) return false;
     // short lists: the copy of the neighbourhood is not earned back (the
@@ -439,7 +465,15 @@ bool plan_bricks(md_ctx c) {
     if (!cells && (double)d.n / d.volume * 4.0 / 3.0 * M_PI * side * side * side < 48.0)
       return false;
     if (slots((double)d.n / ((double)d.nc * d.nc * d.nc), 1, 1, 1) >= most) return false;
+    const Shape b = shape(d);
+    auto along = [&](int32_t t) { return (int64_t)((d.nc + t - 1) / t); };
+    tiles += along(b.x) * along(b.y) * along(b.z);
   }
+  // a launch holds fewer than 2^32 threads, and a force launch one block of at
+  // most 512 per tile (of 1,024 where there are at most 256 blocks): 8.4
+  // million tiles, which only list-free boxes of some 10^9 particles reach when
+  // they are dilute; row tiles take them
+  if (tiles > 0xffffffffll / (64 * search_waves())) return false;
   c->btiles_h.clear();
   c->bricks_h.clear();
   c->brick_parts = 0;
@@ -450,22 +484,9 @@ bool plan_bricks(md_ctx c) {
     RepDesc& d = c->reps_h[r];
     const int32_t nc = d.nc;
     const double ppc = (double)d.n / ((double)nc * nc * nc);
-    int bx = 1, by = 1, bz = 1;
-    auto fits = [&](int32_t room) {
-      bx = by = bz = 1;
-      for (int x = 1; x <= std::min(4, nc); ++x)
-        for (int y = 1; y <= x; ++y)
-          for (int z = 1; z <= y; ++z) {
-            const double homes = ppc * x * y * z;
-            if (homes > 240.0 || slots(ppc, x, y, z) >= room) continue;
-            const int v = x * y * z, bv = bx * by * bz;
-            const int h = (x + 2) * (y + 2) * (z + 2), bh = (bx + 2) * (by + 2) * (bz + 2);
-            if (v > bv || (v == bv && h < bh)) bx = x, by = y, bz = z;
-          }
-      return bx * by * bz;
-    };
-    if (fits(std::min(most, kBrickSlots)) < 8) fits(most);
-    const bool rbig = slots(ppc, bx, by, bz) >= kBrickSlots;
+    const Shape sh = shape(d);
+    const int32_t bx = sh.x, by = sh.y, bz = sh.z;
+    const bool rbig = sh.big;
     const int32_t pass = nlist_brick_pass(rbig);
     big |= rbig;
     // bricks of a tile: the matrix product takes 32 homes at a time against

@@ -4,6 +4,9 @@
 //     a box whose particles fill the lower FILL of its height: home rows of
 //     every tile from the cell counts, and the index that every load of a
 //     home particle uses
+//   brick_plan_host grid N RHO
+//     the list-free path: threads of a force launch, which one launch holds
+//     and its 32-bit index counts
 #include "../paper_1105_5613_amd/csrc/md_api.cpp"
 
 #include <cstdlib>
@@ -80,12 +83,25 @@ int empty(int64_t n, double rho, double fill) {
   return empty_tiles && at_end ? 0 : 3;
 }
 
+int grid(int64_t n, double rho) {
+  md_ctx_s c;
+  const double rc[3] = {2.5, 2.0, 2.2};
+  one_box(&c, n, rho, MD_PATH_CELLS, rc, 0.3);
+  if (!plan_bricks(&c)) return std::puts("row tiles"), c.ba.ntiles != 0 || c.brick_parts != 0;
+  const int64_t threads = (int64_t)c.ba.ntiles * c.search_threads;
+  std::printf("%d tiles of %d threads: %.3f of 2^32\n", c.ba.ntiles, c.search_threads,
+              (double)threads / 4294967296.0);
+  // the clear of the cell counts reaches every cell
+  return threads >= (1ll << 32) || threads < c.ncells;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "empty" && argc == 5)
     return empty(std::atoll(argv[2]), std::atof(argv[3]), std::atof(argv[4]));
+  if (what == "grid" && argc == 4) return grid(std::atoll(argv[2]), std::atof(argv[3]));
   std::puts("unknown check");
   return 4;
 }

@@ -35,3 +35,13 @@ def test_empty_tiles_read_no_particle(plan, n, rho, fill):
     """Boxes with a void at the top: their last tiles hold no home particles and
     their home rows start past the last particle."""
     print(plan("empty", n, rho, fill))
+
+
+@pytest.mark.parametrize("n,rho,tiles", [(1 << 20, 1.2, True), (1 << 20, 0.05, True),
+                                         (900000000, 1.2, True), (1 << 30, 0.05, False)])
+def test_list_free_launches_fit_a_grid(plan, n, rho, tiles):
+    """At 900,000,000 particles the threads of a launch pass 2^31; a dilute box
+    of 2^30 would pass 2^32 and takes row tiles."""
+    out = plan("grid", n, rho)
+    print(out)
+    assert ("tiles of" in out) == tiles
