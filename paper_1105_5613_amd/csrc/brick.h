@@ -36,8 +36,13 @@ constexpr int32_t kUnitHomes = 64;              // each of 64 homes (the last on
 constexpr int32_t kTileRows = 36;               // rows of a neighbourhood: (ty + 2)(tz + 2), t <= 4
 constexpr int32_t kTileHomeRows = 16;           // rows of home cells: ty * tz
 constexpr int32_t kBrickThreads = 1024;         // most threads per block of the force kernel
-constexpr int32_t kChunksAhead = 4;         // chunks the force kernel may read past a row
+constexpr int32_t kChunksAhead = 1;             // chunks the force kernel may read past a row
 constexpr int32_t kChunkEntries = 8;            // entries per 16-byte list chunk
+// Most chunks of a row: its entries are slots of one neighbourhood, and every
+// pass of the search (of at least 12 chunks of 64 candidates) ends with a chunk
+// that need not be full.
+constexpr int32_t kMostChunks =
+    kBrickSlotsBig / kChunkEntries + (kBrickSlotsBig + 12 * 64 - 1) / (12 * 64);
 
 struct BrickTile {
   int32_t rep;
@@ -72,10 +77,18 @@ struct TileHead {
 };
 
 // Chunk c of the row of particle i is element list_base(i, capc) + c kSlice of
-// the list, in 16-byte units.  One chunk per particle of a slice more than the
-// capacity is allocated: the force kernel reads one chunk ahead.
+// the list, in 16-byte units.  kChunksAhead chunks per particle of a slice more
+// than the capacity are allocated: the force kernel reads ahead.
 inline size_t chunk_elems(int32_t ntot, int32_t capc) {
   return list_elems(ntot, capc) + kChunksAhead * kSlice;
+}
+
+// Whether the rows of every tile lie within 4 GiB of list, which the force
+// kernel addresses with 32 bits from the tile's first one; layer: the most
+// particles that a layer of tiles can hold.
+inline bool list_span_fits(int64_t layer, int32_t capc) {
+  return ((layer / kSlice + 2) * capc + kChunksAhead) * kSlice * (int64_t)sizeof(uint4) <
+         (int64_t)1 << 32;
 }
 
 __device__ inline void wrap_cell(int32_t& q, int32_t nc, int32_t& s) {

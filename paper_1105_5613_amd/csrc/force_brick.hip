@@ -43,6 +43,7 @@ namespace {
 constexpr int kTaskHomes = 16;  // homes per partial of the energies
 constexpr double kFarAway = 1.0e300;
 constexpr int kAhead = 1;  // list chunks read ahead (2, 3 and 4 measured the same)
+static_assert(kAhead <= kChunksAhead, "chunk_elems allocates what is read ahead");
 
 template <typename T>
 struct EnergyTab {
@@ -215,7 +216,7 @@ __attribute__((amdgpu_waves_per_eu(EN || BIG || (!MIXED && TPP == 2) ? 4 : 6))) 
     int32_t i = me.i;
     const double4 p = me.p;
     const int32_t ti = (int32_t)p.w;
-    // list bytes from the tile's first particle on fit 32 bits (plan_bricks)
+    // list bytes from the tile's first particle on fit 32 bits (list_span_fits)
     uint32_t at_row = (uint32_t)((list_base(i, A.capc) - base) * sizeof(uint4)) + lp * 2 * E;
     constexpr uint32_t kStep = kSlice * sizeof(uint4);
     // constants of the home particle's species against either partner species
@@ -350,7 +351,7 @@ __attribute__((amdgpu_waves_per_eu(EN || BIG || (!MIXED && TPP == 2) ? 4 : 6))) 
 #pragma unroll
     for (int k = 0; k < kAhead; ++k) load(e[k]);
     for (int32_t c = 0; c < me.nch; ++c) {
-      load(e[kAhead]);  // the chunks past a row's last one are allocated
+      load(e[kAhead]);  // the chunks past a row's last one are allocated (chunk_elems)
       // two entries in flight: four held 24 registers and spilled at 80 in the
       // mixed form (166 us per launch, 145 so; FP64 201, 198)
 #pragma unroll

@@ -68,6 +68,7 @@ struct md_ctx_s {
   int32_t brick_parts = 0;   // partials of the force kernel
   double brick_homes = 0.0;  // expected home particles of the fullest tile
   int32_t brick_extra = 0;   // list chunks beyond the capacity's (one per pass but the first)
+  int64_t brick_layer = 0;   // most particles of a layer of tiles (list_span_fits)
   int32_t any_multi = 0;  // some replica has >= 3 cells per side
   int32_t ntiles1 = 0;    // tiles of the replicas with one cell
   Tile* tiles1 = nullptr;
@@ -392,6 +393,12 @@ BrickPair brick_pair(const md_params& p, const PairTab& t) {
   return b;
 }
 
+// List chunks per particle on the brick path for a capacity in entries.
+int32_t chunk_capacity(md_ctx c, int32_t cap) {
+  const int64_t chunks = ((int64_t)cap + kChunkEntries - 1) / kChunkEntries;
+  return (int32_t)std::min<int64_t>(chunks + c->brick_extra, kMostChunks);
+}
+
 // Whether the context takes the brick path, or on MD_PATH_CELLS the search on
 // tiles of cells, and its tiles and bricks.  Conditions: MD_PATH_AUTO with no
 // force variant asked for by tpp or unroll (those name gather variants), or
@@ -455,6 +462,7 @@ bool plan_bricks(md_ctx c) {
     return b;
   };
   int64_t tiles = 0;
+  c->brick_layer = 0;
   for (const RepDesc& d : c->reps_h) {
     if (d.nc < 3) return false;
     // short lists: the copy of the neighbourhood is not earned back (the
@@ -468,7 +476,16 @@ bool plan_bricks(md_ctx c) {
     const Shape b = shape(d);
     auto along = [&](int32_t t) { return (int64_t)((d.nc + t - 1) / t); };
     tiles += along(b.x) * along(b.y) * along(b.z);
+    // a layer of tiles: each holds its cells and those around them in the
+    // slots, and in tiles up to two cells wide every cell is counted twice
+    const int64_t twice = (b.x <= 2 ? 2 : 1) * (b.y <= 2 ? 2 : 1);
+    const int64_t layer = (along(b.x) * along(b.y) * (kBrickSlotsBig - 1) + twice - 1) / twice;
+    c->brick_layer = std::max(c->brick_layer, std::min<int64_t>(d.n, layer));
   }
+  // (with the default capacity: up to 2^26 particles, the most of the path)
+  if (!cells &&
+      !list_span_fits(c->brick_layer, std::min(kMostChunks, c->cap / kChunkEntries + 5)))
+    return false;
   // a launch holds fewer than 2^32 threads, and a force launch one block of at
   // most 512 per tile (of 1,024 where there are at most 256 blocks): 8.4
   // million tiles, which only list-free boxes of some 10^9 particles reach when
@@ -583,6 +600,7 @@ bool plan_bricks(md_ctx c) {
 }
 
 void drop_graph(md_ctx c);
+md_status leave_brick(md_ctx c);
 
 // Grow the neighbour capacity after an overflowed build to the longest row it
 // found plus 16 (never below the old capacity).  The rows already built move
@@ -606,7 +624,8 @@ md_status grow_capacity(md_ctx c) {
   const int32_t cap = std::max(c->cap, ((m + 16 + 7) / 8) * 8);
   if (c->brick) {
     uint4* fresh = nullptr;
-    const int32_t capc = cap / kChunkEntries + c->brick_extra;
+    const int32_t capc = chunk_capacity(c, cap);
+    if (!list_span_fits(c->brick_layer, capc)) return leave_brick(c);
     md_status rc = dalloc(c, &fresh, chunk_elems(c->ntot, capc));
     if (rc) return rc;
     launch_relayout_chunks(c->stream, c->ntot, c->ba.nchunk, c->ba.capc, capc, c->ba.list, fresh);
@@ -699,7 +718,7 @@ md_status alloc_gather(md_ctx c) {
 
 // A tile whose neighbourhood outgrew the LDS slots (a box that condensed far
 // above its mean density): the context goes on with gather lists, which take
-// any density.  The caller rebuilds every replica.  Nothing is switched before
+// any density.  Every replica is marked for a rebuild.  Nothing is switched before
 // the gather buffers are there: a call that fails here leaves the context on
 // its tiles, to try again at the next build.  (Where the two lists do not fit
 // side by side, the tiles' is given back first; build_all asks for it again.)
@@ -720,6 +739,7 @@ md_status leave_brick(md_ctx c) {
   c->unroll = 4;
   gather_blocks(c);
   drop_graph(c);
+  launch_mark_rebuild(c->stream, c->nrep, c->rebuild, c->st);
   return upload_blocks(c);
 }
 
@@ -730,6 +750,7 @@ md_status leave_search(md_ctx c) {
   c->ba.ntiles = 0;
   row_tile_blocks(c);
   drop_graph(c);
+  launch_mark_rebuild(c->stream, c->nrep, c->rebuild, c->st);
   return upload_blocks(c);
 }
 
@@ -756,8 +777,9 @@ md_status build_all(md_ctx c) {
       rc = c->brick ? leave_brick(c) : leave_search(c);
     } else {
       if (grown) return rc;
-      grown = true;
+      const bool tiles = c->brick;
       rc = grow_capacity(c);
+      grown = c->brick == tiles;  // or it went on with gather lists
     }
     if (rc) return rc;
   }
@@ -1080,6 +1102,12 @@ md_status md_init_alloc(md_ctx* out, const md_params* p, int32_t nrep, const int
         return fail(nullptr, MD_EINVAL,
                     "mixed precision on the gather path supports up to 1023 cells per side");
       }
+  if (p->max_neighbors > 0) {
+    c->cap = p->max_neighbors;
+  } else {
+    const double expect = rho_max * 4.0 / 3.0 * M_PI * side * side * side;
+    c->cap = (int32_t)(((int64_t)std::ceil(1.5 * expect) + 16 + 7) / 8 * 8);
+  }
   int32_t lds_max = 65536;
   {
     int dev = 0, v = 0;
@@ -1139,13 +1167,6 @@ md_status md_init_alloc(md_ctx* out, const md_params* p, int32_t nrep, const int
   } else {
     gather_blocks(c);
   }
-  if (p->max_neighbors > 0) {
-    c->cap = p->max_neighbors;
-  } else {
-    const double expect = rho_max * 4.0 / 3.0 * M_PI * side * side * side;
-    c->cap = (int32_t)(((int64_t)std::ceil(1.5 * expect) + 16 + 7) / 8 * 8);
-  }
-
   // pair table: shift constants of Eq. (3) computed on the host in FP64
   PairTab tab{};
   for (int a = 0; a < MD_MAXT; ++a)
@@ -1229,7 +1250,7 @@ md_status md_init_alloc(md_ctx* out, const md_params* p, int32_t nrep, const int
   ALLOC(c->id_tmp, N);
   ALLOC(c->img, 3 * N);
   if (c->brick || c->search) {
-    c->ba.capc = (c->cap + kChunkEntries - 1) / kChunkEntries + c->brick_extra;
+    c->ba.capc = chunk_capacity(c, c->cap);
     BrickTile* bt = nullptr;
     Brick* br = nullptr;
     ALLOC(bt, (size_t)c->ba.ntiles);
@@ -1464,10 +1485,6 @@ md_status md_step(md_ctx c, int32_t nsteps, const double* T0, const double* T1,
     HIPCHECK(c, hipMemcpy(&done, c->kcall, sizeof(int64_t), hipMemcpyDeviceToHost));
     if (st.err & kErrSlots) {
       rc = c->brick ? leave_brick(c) : leave_search(c);
-      if (!rc) {
-        launch_mark_rebuild(s, c->nrep, c->rebuild, c->st);
-        HIPCHECK(c, hipStreamSynchronize(s));
-      }
     } else {
       rc = grow_capacity(c);
     }
@@ -1550,16 +1567,18 @@ md_status md_get_neighbors(md_ctx c, int32_t rep, int32_t* count, int32_t* ids, 
                         hipMemcpyDeviceToHost));
   HIPCHECK(c, hipMemcpy(idv.data(), c->id, sizeof(int32_t) * c->ntot, hipMemcpyDeviceToHost));
   // the list slices that hold the replica's particles, one contiguous block
+  // (decoded from the tiles: as many entries as a row there can have)
+  const int32_t lcap = c->brick ? std::min(c->cap, c->ba.capc * kChunkEntries) : c->cap;
   const int32_t s0 = (int32_t)(d.off / kSlice), s1 = (int32_t)((d.off + d.n - 1) / kSlice);
-  const size_t lo = (size_t)s0 * kSlice * c->cap, nel = (size_t)(s1 - s0 + 1) * kSlice * c->cap;
+  const size_t lo = (size_t)s0 * kSlice * lcap, nel = (size_t)(s1 - s0 + 1) * kSlice * lcap;
   std::vector<uint32_t> sl(cap > 0 && d.n > 0 ? nel : 1);
   if (cap > 0 && d.n > 0) {
     const uint32_t* src = c->nbr;
     uint32_t* tmp = nullptr;
     if (c->brick) {
-      md_status a_rc = dalloc(c, &tmp, list_elems(c->ntot, c->cap));
+      md_status a_rc = dalloc(c, &tmp, list_elems(c->ntot, lcap));
       if (a_rc) return a_rc;
-      launch_decode_brick(c->stream, c->ba, c->cap, c->ncount, tmp);
+      launch_decode_brick(c->stream, c->ba, lcap, c->ncount, tmp);
       HIPCHECK(c, hipStreamSynchronize(c->stream));
       src = tmp;
     } else if (c->staged) {
@@ -1578,8 +1597,8 @@ md_status md_get_neighbors(md_ctx c, int32_t rep, int32_t* count, int32_t* ids, 
     const int32_t g = (int32_t)d.off + i;
     const int32_t orig = idv[g] - d.off;
     count[orig] = cnt[i];
-    const int32_t m = std::min(std::min(cnt[i], c->cap), cap);
-    const size_t b = list_base(g, c->cap) - lo;
+    const int32_t m = std::min(std::min(cnt[i], lcap), cap);
+    const size_t b = list_base(g, lcap) - lo;
     for (int32_t k = 0; k < m; ++k) {
       const uint32_t e = sl[b + (size_t)k * kSlice];
       ids[(size_t)orig * cap + k] = idv[e & kIdxMask] - d.off;

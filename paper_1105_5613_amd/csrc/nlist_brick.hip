@@ -51,6 +51,7 @@ constexpr int kNbGroup = 32;    // home particles per group (columns of the prod
 // candidates: with 12 it took two passes (64 replicas of 1,000 to 65,536, a
 // fifth rebuilding: 167 us per launch, 158 with 15).
 constexpr int kNbChunks = 12, kNbChunksBig = 15;
+static_assert(kNbChunks >= 12 && kNbChunksBig >= 12, "kMostChunks counts on passes of 12");
 constexpr int kNbWaves = 4;     // bricks per block
 constexpr int kCoopWaves = 8;   // waves per brick (COOP)
 constexpr int kCoopBlocks = 1024;  // most blocks of the COOP form

@@ -7,6 +7,9 @@
 //   brick_plan_host grid N RHO
 //     the list-free path: threads of a force launch, which one launch holds
 //     and its 32-bit index counts
+//   brick_plan_host span N RHO CAP
+//     the list path with a capacity of CAP entries (0: the default one): bytes
+//     of list that the rows of a layer of tiles can take
 #include "../paper_1105_5613_amd/csrc/md_api.cpp"
 
 #include <cstdlib>
@@ -95,6 +98,24 @@ int grid(int64_t n, double rho) {
   return threads >= (1ll << 32) || threads < c.ncells;
 }
 
+int span(int64_t n, double rho, int32_t cap) {
+  md_ctx_s c;
+  const double rc[3] = {2.5, 2.0, 2.2};
+  one_box(&c, n, rho, MD_PATH_AUTO, rc, 0.3);
+  c.cap = cap ? cap : (int32_t)std::ceil(1.5 * rho * 4.0 / 3.0 * M_PI * 2.8 * 2.8 * 2.8) + 24;
+  if (!plan_bricks(&c)) return std::puts("gather lists"), c.ba.ntiles != 0;
+  const RepDesc& d = c.reps_h[0];
+  c.ba.capc = chunk_capacity(&c, c.cap);
+  int64_t layer = 0;  // particles at the mean density between a tile's first and last home
+  for (const BrickTile& T : c.btiles_h)
+    layer = std::max<int64_t>(
+        layer, (int64_t)((double)n / c.ncells * (((T.tz - 1) * d.nc + T.ty - 1) * d.nc + T.tx)));
+  std::printf("tiles of cells: %d chunks a row, %lld particles, at most %lld: %.3f of 4 GiB\n",
+              c.ba.capc, (long long)layer, (long long)c.brick_layer,
+              (double)(c.brick_layer / kSlice + 2) * c.ba.capc * kSlice * 16 / 4294967296.0);
+  return layer > c.brick_layer || !list_span_fits(c.brick_layer, c.ba.capc);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -102,6 +123,8 @@ int main(int argc, char** argv) {
   if (what == "empty" && argc == 5)
     return empty(std::atoll(argv[2]), std::atof(argv[3]), std::atof(argv[4]));
   if (what == "grid" && argc == 4) return grid(std::atoll(argv[2]), std::atof(argv[3]));
+  if (what == "span" && argc == 5)
+    return span(std::atoll(argv[2]), std::atof(argv[3]), std::atoi(argv[4]));
   std::puts("unknown check");
   return 4;
 }

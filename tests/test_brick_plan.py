@@ -45,3 +45,16 @@ def test_list_free_launches_fit_a_grid(plan, n, rho, tiles):
     out = plan("grid", n, rho)
     print(out)
     assert ("tiles of" in out) == tiles
+
+
+@pytest.mark.parametrize("n,rho,cap,tiles", [
+    (4000, 1.2, 0, True), (1 << 20, 1.2, 0, True), (1 << 24, 1.2, 0, True),
+    (1 << 26, 1.2, 0, True), (1 << 26, 0.6, 0, True), (6000, 1.2, 2400000, True),
+    (1 << 20, 1.2, 2 ** 31 - 1, True), (1 << 26, 1.2, 4000, False)])
+def test_rows_of_a_tile_within_32_bits(plan, n, rho, cap, tiles):
+    """The force kernel addresses the list from a tile's first row with 32
+    bits: rows are never given more chunks than a neighbourhood has entries
+    for, and boxes where that is not enough keep gather lists."""
+    out = plan("span", n, rho, cap)
+    print(out)
+    assert ("tiles of" in out) == tiles
