@@ -135,6 +135,7 @@ struct md_ctx_s {
   size_t ev_used = 0;
   bool has_state = false, built = false, forces_valid = false;
   std::string err;
+  int32_t err_bits = 0;  // device error bits behind the last failure of sync_and_check
 };
 
 namespace {
@@ -247,13 +248,15 @@ md_status sync_and_check(md_ctx c) {
   HIPCHECK(c, hipStreamSynchronize(c->stream));
   DevState st{};
   HIPCHECK(c, hipMemcpy(&st, c->st, sizeof(DevState), hipMemcpyDeviceToHost));
+  c->err_bits = st.err;
   if (st.err) {
     DevState z{};
     HIPCHECK(c, hipMemcpy(c->st, &z, sizeof(DevState), hipMemcpyHostToDevice));
     if (st.err & kErrSlots)
       return fail(c, MD_EOVERFLOW,
-                  "a staged row tile's neighbourhood exceeds 16383 LDS slots (use smaller "
-                  "tile_cells)");
+                  c->staged ? "a staged row tile's neighbourhood exceeds 16383 LDS slots (use "
+                              "smaller tile_cells)"
+                            : "a tile's neighbourhood exceeds its LDS slots");
     if (st.err & kErrOverflow)
       return fail(c, MD_EOVERFLOW, "neighbour list capacity exceeded");
     if (st.err & kErrType) return fail(c, MD_EINVAL, "species index out of range");
@@ -772,7 +775,7 @@ md_status build_all(md_ctx c) {
       return MD_OK;
     }
     if (rc != MD_EOVERFLOW) return rc;
-    if (c->err.find("LDS slots") != std::string::npos) {  // not a capacity
+    if (c->err_bits & kErrSlots) {  // not a capacity
       if (!c->brick && !c->search) return rc;
       rc = c->brick ? leave_brick(c) : leave_search(c);
     } else {
