@@ -81,10 +81,14 @@ enum { MD_FP64 = 0, MD_MIXED = 1 };
  * that fit a block's LDS, and tpp and unroll are 0: a block copies a tile's
  * neighbourhood into LDS and walks 16-bit list entries against it, and the
  * list search is a matrix product with an exact FP64 test of the pairs near
- * the cutoff.  The partners, and so md_get_neighbors, are GATHER's; a box that
- * condenses beyond the LDS goes on with gather lists.  Elsewhere AUTO is
+ * the cutoff.  The partners, and so md_get_neighbors, are GATHER's.  Elsewhere AUTO is
  * GATHER.  CELLS runs on the same tiles with tile_cells = 0, by row tiles
- * otherwise or in boxes too dense for them. */
+ * otherwise or in boxes too dense for them.  The choice is one for all replicas
+ * of the context: one that does not fit the tiles takes all of them elsewhere.
+ * A context in which some box condenses beyond the LDS slots of its tiles goes
+ * on with gather lists (CELLS: row tiles), all replicas being rebuilt once for
+ * it, until the next md_set_state; both paths sum in their own order, so that
+ * results then differ from those on the tiles by rounding. */
 enum { MD_PATH_AUTO = 0, MD_PATH_GATHER = 1, MD_PATH_STAGED = 2, MD_PATH_CELLS = 3 };
 #define MD_MAXT 4
 

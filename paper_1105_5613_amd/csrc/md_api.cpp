@@ -69,6 +69,7 @@ struct md_ctx_s {
   double brick_homes = 0.0;  // expected home particles of the fullest tile
   int32_t brick_extra = 0;   // list chunks beyond the capacity's (one per pass but the first)
   int64_t brick_layer = 0;   // most particles of a layer of tiles (list_span_fits)
+  int32_t brick_tpp = 0, brick_unroll = 0;  // variant to return to the tiles with (enter_tiles)
   int32_t any_multi = 0;  // some replica has >= 3 cells per side
   int32_t ntiles1 = 0;    // tiles of the replicas with one cell
   Tile* tiles1 = nullptr;
@@ -421,9 +422,10 @@ int32_t chunk_capacity(md_ctx c, int32_t cap) {
 // three blocks fit a CU, is taken where it holds eight home cells: nine in the
 // larger one (16,777,216 particles, 26.4 per cell) took 2,855 us per mixed
 // launch, eight here 2,545; with six or seven the larger one is the faster (262,144
-// particles, 28.3 per cell: 103 us a step, six cells in the smaller 120).  The rule
-// looks at the density of one replica only, so that a replica's sums are the
-// same alone and in a batch.
+// particles, 28.3 per cell: 103 us a step, six cells in the smaller 120).  A
+// replica's tiles follow from its own density only, so that its sums on them are
+// the same alone and in a batch.  Whether the context takes them is decided by
+// all its replicas together.
 bool plan_bricks(md_ctx c) {
   const md_params& p = c->p;
   const bool cells = c->cells;  // for the list-free search
@@ -604,6 +606,8 @@ bool plan_bricks(md_ctx c) {
 
 void drop_graph(md_ctx c);
 md_status leave_brick(md_ctx c);
+void free_gather(md_ctx c);
+void free_chunks(md_ctx c);
 
 // Grow the neighbour capacity after an overflowed build to the longest row it
 // found plus 16 (never below the old capacity).  The rows already built move
@@ -634,7 +638,8 @@ md_status grow_capacity(md_ctx c) {
     launch_relayout_chunks(c->stream, c->ntot, c->ba.nchunk, c->ba.capc, capc, c->ba.list, fresh);
     HIPCHECK(c, hipGetLastError());
     HIPCHECK(c, hipStreamSynchronize(c->stream));
-    dfree(c, c->ba.list);
+    free_chunks(c);
+    free_gather(c);  // of the old capacity, where a switch left one
     c->ba.list = fresh;
     c->ba.capc = capc;
     c->cap = cap;
@@ -703,6 +708,7 @@ md_status upload_blocks(md_ctx c) {
 
 // The buffers of the gather path, all of them or none.
 md_status alloc_gather(md_ctx c) {
+  if (c->nbr) return MD_OK;
   uint32_t* nbr = nullptr;
   int4 *rec = nullptr, *alt = nullptr;
   md_status rc = dalloc(c, &nbr, list_elems(c->ntot, c->cap));
@@ -719,18 +725,41 @@ md_status alloc_gather(md_ctx c) {
   return MD_OK;
 }
 
+void free_gather(md_ctx c) {
+  dfree(c, c->nbr);
+  dfree(c, c->pos16);
+  dfree(c, c->pos16_alt);
+  c->nbr = nullptr;
+  c->pos16 = c->pos16_alt = nullptr;
+}
+
+void free_chunks(md_ctx c) {
+  dfree(c, c->ba.list);
+  c->ba.list = nullptr;
+}
+
+// The buffers of the path that the context is on; a switch that failed for want
+// of memory may have given them back.
+md_status path_buffers(md_ctx c) {
+  if (c->brick && !c->ba.list)
+    return dalloc(c, &c->ba.list, chunk_elems(c->ntot, c->ba.capc));
+  return c->brick || c->staged || c->cells ? MD_OK : alloc_gather(c);
+}
+
 // A tile whose neighbourhood outgrew the LDS slots (a box that condensed far
-// above its mean density): the context goes on with gather lists, which take
-// any density.  Every replica is marked for a rebuild.  Nothing is switched before
-// the gather buffers are there: a call that fails here leaves the context on
-// its tiles, to try again at the next build.  (Where the two lists do not fit
-// side by side, the tiles' is given back first; build_all asks for it again.)
+// above its mean density): the context, with all its replicas, goes on with
+// gather lists, which take any density, until the next md_set_state
+// (enter_tiles).  Every replica is marked for a rebuild.  Nothing is switched
+// before the gather buffers are there: a call that fails here leaves the context
+// on its tiles, to try again at the next build.  Both lists are kept from then
+// on, as long as they fit side by side.
 md_status leave_brick(md_ctx c) {
   HIPCHECK(c, hipStreamSynchronize(c->stream));
   md_status rc = alloc_gather(c);
-  dfree(c, c->ba.list);
-  c->ba.list = nullptr;
-  if (rc) rc = alloc_gather(c);
+  if (rc) {
+    free_chunks(c);
+    rc = alloc_gather(c);
+  }
   if (rc) {
     c->built = c->forces_valid = false;
     return rc;
@@ -738,6 +767,8 @@ md_status leave_brick(md_ctx c) {
   c->ba.ntiles = 0;
   c->ba.nbricks = 0;
   c->brick = false;
+  c->brick_tpp = c->tpp;
+  c->brick_unroll = c->unroll;
   c->tpp = 2;
   c->unroll = 4;
   gather_blocks(c);
@@ -757,18 +788,48 @@ md_status leave_search(md_ctx c) {
   return upload_blocks(c);
 }
 
+// A new state starts on the tiles again if the context left them, so that it is
+// evaluated as in a new context.  (Without memory for their list it stays on
+// gather lists.)
+md_status enter_tiles(md_ctx c) {
+  if (c->brick || c->search || c->btiles_h.empty()) return MD_OK;
+  HIPCHECK(c, hipStreamSynchronize(c->stream));
+  if (!c->cells) {
+    const int32_t capc = chunk_capacity(c, c->cap);  // it may have grown since
+    if (!list_span_fits(c->brick_layer, capc)) return MD_OK;
+    if (capc != c->ba.capc) free_chunks(c);
+    c->ba.capc = capc;
+    if (!c->ba.list && dalloc(c, &c->ba.list, chunk_elems(c->ntot, capc))) {
+      free_gather(c);
+      if (dalloc(c, &c->ba.list, chunk_elems(c->ntot, capc))) return MD_OK;
+    }
+    c->tpp = c->brick_tpp;
+    c->unroll = c->brick_unroll;
+  }
+  c->brick = !c->cells;
+  c->search = c->cells;
+  c->ba.ntiles = (int32_t)c->btiles_h.size();
+  c->ba.nbricks = (int32_t)c->bricks_h.size();
+  for (const BrickTile& t : c->btiles_h) {  // a replica's tiles follow each other
+    RepDesc& d = c->reps_h[t.rep];
+    if (t.cx == 0 && t.cy == 0 && t.cz == 0) d.fb0 = t.part;
+    d.fb1 = t.part + t.units;
+  }
+  drop_graph(c);
+  return upload_blocks(c);
+}
+
 // Full rebuild of every replica (md_build_cells and the first build after
 // md_set_state); grows the neighbour capacity once on overflow.
 md_status build_all(md_ctx c) {
-  if (c->brick && !c->ba.list) {  // given back by a leave_brick that failed
-    const md_status rc = dalloc(c, &c->ba.list, chunk_elems(c->ntot, c->ba.capc));
-    if (rc) return rc;
-  }
+  if (const md_status rc = path_buffers(c)) return rc;
   for (bool grown = false;;) {
     launch_mark_rebuild(c->stream, c->nrep, c->rebuild, c->st);
     run_chain(c, c->stream);
-    launch_after_build(c->stream, c->nrep, c->rebuild, c->obs, c->st);
     md_status rc = sync_and_check(c);
+    // counted as a build, unless the context leaves its tiles for it
+    if (!(c->err_bits & kErrSlots) || c->staged)
+      launch_after_build(c->stream, c->nrep, c->rebuild, c->obs, c->st);
     if (rc == MD_OK) {
       c->built = true;
       c->forces_valid = false;
@@ -868,7 +929,7 @@ md_status enqueue_step(md_ctx c, hipStream_t s, const ThermoArgs& ta, int32_t th
   const int32_t nzero = zero_in_kick ? c->ncells : 0;
   if (kick && !resume)
     launch_kick_drift(s, c->mixed, thermo, c->ntiles, c->tiles, c->reps, c->tab, c->pos,
-                      c->pos16, c->vel, c->frc, c->xref, c->stride, c->p.dt, c->lam, c->rebuild,
+                      c->brick ? nullptr : c->pos16, c->vel, c->frc, c->xref, c->stride, c->p.dt, c->lam, c->rebuild,
                       c->dmax, c->st, c->counts, nzero);
   run_chain(c, s, zero_in_kick && !resume);
   const bool timed = c->prof_every > 0 && (k + 1) % c->prof_every == 0;
@@ -1356,6 +1417,7 @@ md_status md_destroy(md_ctx c) {
 md_status md_set_state(md_ctx c, const double* x, const double* v, const int32_t* type) {
   if (!c) return MD_EINVAL;
   if (!x || !v || !type) return fail(c, MD_EINVAL, "x, v and type are required");
+  if (const md_status e = enter_tiles(c)) return e;
   launch_set_state(c->stream, c->ntot, c->stride, x, v, type, c->p.ntypes, c->pos, c->vel, c->id,
                    c->img, c->st);
   HIPCHECK(c, hipMemsetAsync(c->obs, 0, sizeof(md_obs) * c->nrep, c->stream));
