@@ -55,10 +55,13 @@ __device__ inline int32_t cell_coord(double c, double inv_cell, int32_t nc) {
 // (the next double above L / 2 divides to a quotient above 1/2; the tie
 // d = L / 2 rounds to 0), and no division is needed.  The box holds a few
 // hundred particles, so the time is latency: 500 particles took 156 us with
-// one thread per particle, 7.1 us with one wave.
+// one thread per particle, 7.1 us with one wave.  Batches of them take at most
+// kGatedGrid blocks, which loop: 2,048 replicas of 500 particles had 262,144
+// blocks, and a step, on which a few replicas rebuild, took 632 us with them,
+// 609 looped (mixed 576, 551).
 constexpr int kOneWaves = 4;  // home particles per block
 __global__ __launch_bounds__(64 * kOneWaves) void k_nlist(
-    const Tile* __restrict__ tiles, const RepDesc* __restrict__ reps,
+    int32_t ntiles, const Tile* __restrict__ tiles, const RepDesc* __restrict__ reps,
     const int32_t* __restrict__ rebuild, const PairTab* __restrict__ tab, int32_t stride,
     int32_t cap, const double4* __restrict__ pos_tmp, const double* __restrict__ vel_tmp,
     const int32_t* __restrict__ id_tmp, double4* __restrict__ pos, double* __restrict__ vel,
@@ -68,59 +71,62 @@ __global__ __launch_bounds__(64 * kOneWaves) void k_nlist(
   if (!st->any_rebuild) return;
   if (threadIdx.x < 16) s_thr[threadIdx.x] = tab->thr[threadIdx.x];
   __syncthreads();
-  constexpr int32_t kBlocks = kTile / kOneWaves;  // blocks per tile
-  const Tile t = tiles[blockIdx.x / kBlocks];
-  if (!rebuild[t.rep]) return;
+  constexpr int32_t kBlocks = kTile / kOneWaves;  // of a tile
   const int lane = threadIdx.x & 63;
-  const int32_t i = t.start + (int32_t)(blockIdx.x % kBlocks) * kOneWaves +
-                    __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (i >= t.end) return;
-  const RepDesc R = reps[t.rep];
-  const double4 p = pos_tmp[i];
-  const int32_t ti = (int32_t)p.w;
-  const double* thr = &s_thr[ti * 4];
-  const double half = 0.5 * R.L;
-  int32_t cnt = 0;
-  uint32_t* out = nbr + list_base(i, cap);
-  for (int32_t j0 = R.off; j0 < R.off + R.n; j0 += 64) {
-    const int32_t j = j0 + lane;
-    const bool valid = (j < R.off + R.n) & (j != i);
-    const double4 q = pos_tmp[valid ? j : i];
-    double ex = q.x - p.x, ey = q.y - p.y, ez = q.z - p.z;
-    const int32_t kx = ex > half ? 1 : (ex < -half ? -1 : 0),
-                  ky = ey > half ? 1 : (ey < -half ? -1 : 0),
-                  kz = ez > half ? 1 : (ez < -half ? -1 : 0);
-    ex = ex - R.L * (double)kx;
-    ey = ey - R.L * (double)ky;
-    ez = ez - R.L * (double)kz;
-    const double r2 = (ex * ex + ey * ey) + ez * ez;
-    const bool hit = valid & (r2 < thr[(int32_t)q.w]);
-    const uint64_t m = __builtin_amdgcn_ballot_w64(hit);
-    const int32_t row = cnt + __popcll(m & ((1ull << lane) - 1ull));
-    if (hit && row < cap) {
-      // image s = -k; with one cell d = -s nc = k
-      const uint32_t code = dcode ? image_code(kx, ky, kz) : image_code(-kx, -ky, -kz);
-      out[(size_t)row * kSlice] = (uint32_t)j | code;
+  const int32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  auto block = [&](int32_t b) {
+    const Tile t = tiles[b / kBlocks];
+    if (!rebuild[t.rep]) return;
+    const int32_t i = t.start + (b % kBlocks) * kOneWaves + w;
+    if (i >= t.end) return;
+    const RepDesc R = reps[t.rep];
+    const double4 p = pos_tmp[i];
+    const int32_t ti = (int32_t)p.w;
+    const double* thr = &s_thr[ti * 4];
+    const double half = 0.5 * R.L;
+    int32_t cnt = 0;
+    uint32_t* out = nbr + list_base(i, cap);
+    for (int32_t j0 = R.off; j0 < R.off + R.n; j0 += 64) {
+      const int32_t j = j0 + lane;
+      const bool valid = (j < R.off + R.n) & (j != i);
+      const double4 q = pos_tmp[valid ? j : i];
+      double ex = q.x - p.x, ey = q.y - p.y, ez = q.z - p.z;
+      const int32_t kx = ex > half ? 1 : (ex < -half ? -1 : 0),
+                    ky = ey > half ? 1 : (ey < -half ? -1 : 0),
+                    kz = ez > half ? 1 : (ez < -half ? -1 : 0);
+      ex = ex - R.L * (double)kx;
+      ey = ey - R.L * (double)ky;
+      ez = ez - R.L * (double)kz;
+      const double r2 = (ex * ex + ey * ey) + ez * ez;
+      const bool hit = valid & (r2 < thr[(int32_t)q.w]);
+      const uint64_t m = __builtin_amdgcn_ballot_w64(hit);
+      const int32_t row = cnt + __popcll(m & ((1ull << lane) - 1ull));
+      if (hit && row < cap) {
+        // image s = -k; with one cell d = -s nc = k
+        const uint32_t code = dcode ? image_code(kx, ky, kz) : image_code(-kx, -ky, -kz);
+        out[(size_t)row * kSlice] = (uint32_t)j | code;
+      }
+      cnt += __popcll(m);
     }
-    cnt += __popcll(m);
-  }
-  if (lane != 0) return;
-  ncount[i] = cnt;
-  if (cnt > cap) atomicOr(&st->err, kErrOverflow);
-  // the new cell order becomes the live state; the list is built on it
-  if (pos16) {
-    const uint32_t wc = pack_cell(cell_coord(p.x, R.inv_cell, R.nc), cell_coord(p.y, R.inv_cell, R.nc),
-                                  cell_coord(p.z, R.inv_cell, R.nc), ti);
-    pos16[i] = make_recq(p.x, p.y, p.z, wc, R.cside, R.qs);
-  }
-  pos[i] = p;
-  xref[i] = p.x;
-  xref[stride + i] = p.y;
-  xref[2 * (size_t)stride + i] = p.z;
-  vel[i] = vel_tmp[i];
-  vel[stride + i] = vel_tmp[stride + i];
-  vel[2 * (size_t)stride + i] = vel_tmp[2 * (size_t)stride + i];
-  id[i] = id_tmp[i];
+    if (lane != 0) return;
+    ncount[i] = cnt;
+    if (cnt > cap) atomicOr(&st->err, kErrOverflow);
+    // the new cell order becomes the live state; the list is built on it
+    if (pos16) {
+      const uint32_t wc = pack_cell(cell_coord(p.x, R.inv_cell, R.nc), cell_coord(p.y, R.inv_cell, R.nc),
+                                    cell_coord(p.z, R.inv_cell, R.nc), ti);
+      pos16[i] = make_recq(p.x, p.y, p.z, wc, R.cside, R.qs);
+    }
+    pos[i] = p;
+    xref[i] = p.x;
+    xref[stride + i] = p.y;
+    xref[2 * (size_t)stride + i] = p.z;
+    vel[i] = vel_tmp[i];
+    vel[stride + i] = vel_tmp[stride + i];
+    vel[2 * (size_t)stride + i] = vel_tmp[2 * (size_t)stride + i];
+    id[i] = id_tmp[i];
+  };
+  for (int32_t b = blockIdx.x; b < ntiles * kBlocks; b += gridDim.x) block(b);
 }
 
 // One wave per home cell (nc >= 3), in two phases per group of at most
@@ -594,8 +600,8 @@ void launch_nlist(hipStream_t s, int32_t ntiles1, const Tile* tiles1, const RepD
 #undef KN
   }
   if (ntiles1)
-    k_nlist<<<ntiles1 * (kTile / kOneWaves), 64 * kOneWaves, 0, s>>>(
-        tiles1, reps, rebuild, tab, stride, cap, pos_tmp, vel_tmp, id_tmp, pos, vel, id, xref,
+    k_nlist<<<gated_grid(ntiles1 * (kTile / kOneWaves), false), 64 * kOneWaves, 0, s>>>(
+        ntiles1, tiles1, reps, rebuild, tab, stride, cap, pos_tmp, vel_tmp, id_tmp, pos, vel, id, xref,
         nbr, ncount, st, dcode, pos16);
 }
 
