@@ -125,7 +125,8 @@ typedef struct {
                             applies the next step's first half kick and drift (same
                             arithmetic and results, one pass over the particles fewer per
                             step; never on the last step of an md_step call, so the state
-                            it leaves is complete); 1 = always a separate kick/drift
+                            it leaves is complete, nor in the mixed form on tiles of cells
+                            on a step that forms energies); 1 = always a separate kick/drift
                             launch */
   int32_t small_box;     /* 0 = auto: a context of one box of at most 16,384 particles
                             (and 4,096 cells) rebuilds its cells in one launch, and one of

@@ -195,6 +195,11 @@ struct BrickPair {
   // have bit 14 set, p1 for the other; per home species
   double rc2[4][2], a[4][2], b[4][2], fs[4][2];  // FP64: f(r)/r = (a r^-6 + b) r^-8 + fs / r
   float msig2[4][2], mf12[4][2], mfs[4][2];      // mixed, as force.hip's
+  // energies, 12 V* = (a r^-6 + 2 b) r^-6 - 12 f r - v12 with v12 = 12 (vc - rc fs)
+  // in FP64, p1 and d as above; mixed keeps (r - rc) fs and 12 vc apart, the
+  // values for bit 14 clear and set
+  double v12[4][2];
+  float mrc[4][2], mv12[4][2];
   double tiny;                                   // far below the last bit of any r^2
   float mk;                                      // f6 = -mk f12
   int32_t flip;                                  // the species with bit 14 set is `flip`

@@ -29,6 +29,13 @@
 // blocks of eight waves on a CU (51 KB of LDS each).  Measured per launch at
 // 1,048,576 particles, gather -> brick: FP64 264 -> 198 us, mixed 193 -> 145 us.
 //
+// Energies come from what the force has formed, with one constant more per
+// species pair in FP64 and two in the mixed form (BrickPair), from registers;
+// a table in LDS cost six reads per pair, and a force evaluation took longer
+// than by gathers (FP64 / mixed, tables -> so: 131,072 particles 63 -> 54 /
+// 51 -> 38 us, 1,048,576: 258 -> 223 / 218 -> 161 us).  With more than two
+// species the table stays.
+//
 // TPP lanes take one particle: of each 8-entry chunk lane p takes the entries
 // [8 p / TPP, 8 (p + 1) / TPP).  Sums are kept per pair of entries (0-1, 2-3,
 // 4-5, 6-7 of every chunk) and combined in one fixed tree, and energies per 16
@@ -70,7 +77,7 @@ __device__ inline double rsqrt3(double r2) {
 // 96 without (198 us; four lanes at 80 VGPRs: 230 us).
 template <bool MIXED, int MODE, int TPP, bool EN, int NS, bool BIG>
 __global__ __launch_bounds__(kBrickThreads)
-__attribute__((amdgpu_waves_per_eu(EN || BIG || (!MIXED && TPP == 2) ? 4 : 6))) void k_force_brick(
+__attribute__((amdgpu_waves_per_eu(BIG || (EN && NS > 2) || (!MIXED && (EN || TPP == 2)) ? 4 : 6))) void k_force_brick(
     BrickArgs A, const RepDesc* __restrict__ reps, const PairTab* __restrict__ tab,
     const BrickPair* __restrict__ bp, const double4* __restrict__ pos, double* __restrict__ vel,
     void* __restrict__ frc_, int32_t stride, double dt, double* __restrict__ part, DevState* st,
@@ -85,7 +92,7 @@ __attribute__((amdgpu_waves_per_eu(EN || BIG || (!MIXED && TPP == 2) ? 4 : 6))) 
   __shared__ TileRow s_row[kTileRows];
   __shared__ HomeRow s_home[kTileHomeRows];
   __shared__ double s_ke[kTasks], s_pw[EN ? 2 * kTasks : 1], s_d2[kBrickThreads / 64];
-  __shared__ typename std::conditional<EN, EnergyTab<T>, char>::type s_en[1];
+  __shared__ typename std::conditional<EN && (NS > 2), EnergyTab<T>, char>::type s_en[1];
   __shared__ PairRow s_pair[NS > 2 ? 16 : 1];
   __shared__ double s_mass[4], s_im[4];
   const bool halt = halted(st);  // read beside the tile tables
@@ -108,7 +115,7 @@ __attribute__((amdgpu_waves_per_eu(EN || BIG || (!MIXED && TPP == 2) ? 4 : 6))) 
   }
   if (threadIdx.x < 16) {
     const int k = threadIdx.x;
-    if constexpr (EN) {
+    if constexpr (EN && NS > 2) {
       s_en[0].sig2[k] = (T)tab->sig2[k];
       s_en[0].c12[k] = (T)tab->c12[k];
       s_en[0].c6[k] = (T)tab->c6[k];
@@ -242,7 +249,19 @@ __attribute__((amdgpu_waves_per_eu(EN || BIG || (!MIXED && TPP == 2) ? 4 : 6))) 
         df = bp->fs[ti][1];
       }
     }
-    const int32_t flip = bp->flip;
+    // and of the energies
+    double v1 = 0, dv = 0;
+    float mv0 = 0, mv1 = 0, mc0 = 0, mc1 = 0;
+    if constexpr (EN && NS == 2 && !MIXED) {
+      v1 = bp->v12[ti][0];
+      dv = bp->v12[ti][1];
+    }
+    if constexpr (EN && NS == 2 && MIXED) {
+      mv0 = bp->mv12[ti][0];
+      mv1 = bp->mv12[ti][1];
+      mc0 = bp->mrc[ti][0];
+      mc1 = bp->mrc[ti][1];
+    }
     const double tiny = bp->tiny;
     T fx[NA], fy[NA], fz[NA], pe[NA], vw[NA];
     // one pair: entry e, its LDS position, into sum u
@@ -261,7 +280,7 @@ __attribute__((amdgpu_waves_per_eu(EN || BIG || (!MIXED && TPP == 2) ? 4 : 6))) 
         rc2 = s_pair[ab].rc2;
       }
       if (((!MIXED && !EN) | (r2d > tiny)) & (r2d < rc2)) {
-        T a, b, f, fr, rinv, r2i;
+        T a, b, f, fr, rinv, r2i, x6;  // x6: (s/r)^6 (mixed) or r^-6
         if constexpr (NS == 2) {
           const T sl = MIXED ? (T)__int_as_float((int)((e << 16) & 0x40000000u)) : (T)sel;
           a = fma_t(da, sl, a1);
@@ -277,23 +296,34 @@ __attribute__((amdgpu_waves_per_eu(EN || BIG || (!MIXED && TPP == 2) ? 4 : 6))) 
         if constexpr (MIXED) {
           rinv = __builtin_amdgcn_rsqf(r2);
           r2i = rinv * rinv;
-          const float s2 = a * r2i, s6 = s2 * s2 * s2;
-          fr = b * (s6 - mk) * s6 * r2i + f * rinv;
+          const float s2 = a * r2i;
+          x6 = s2 * s2 * s2;
+          fr = b * (x6 - mk) * x6 * r2i + f * rinv;
         } else {
           rinv = rsqrt3(r2d);
           r2i = rinv * rinv;
-          const double r6 = r2i * r2i * r2i;
-          fr = __builtin_fma(__builtin_fma(a, r6, b) * r6, r2i, f * rinv);
+          x6 = r2i * r2i * r2i;
+          fr = __builtin_fma(__builtin_fma(a, x6, b) * x6, r2i, f * rinv);
         }
         fx[u] = fma_t(fr, dx, fx[u]);
         fy[u] = fma_t(fr, dy, fy[u]);
         fz[u] = fma_t(fr, dz, fz[u]);
         if constexpr (EN) {
-          if constexpr (NS == 2) ab = ti * 4 + ((e & 0x4000u) ? flip : 1 - flip);
-          const auto& W = s_en[0];
-          const T s2 = W.sig2[ab] * r2i, s6 = s2 * s2 * s2;
-          pe[u] += W.c12[ab] * (s6 * s6) + W.c6[ab] * s6 - W.vc[ab] -
-                   (r2 * rinv - W.rc[ab]) * W.fs[ab];
+          // twelve times the energy, from what the force has formed (NS = 2)
+          if constexpr (NS == 2 && MIXED) {
+            const bool set = (e & 0x4000u) != 0u;
+            const float h = (r2 * rinv - (set ? mc1 : mc0)) * f;
+            pe[u] += __builtin_fmaf(
+                -12.0f, h, __builtin_fmaf(b, (x6 - (mk + mk)) * x6, -(set ? mv1 : mv0)));
+          } else if constexpr (NS == 2) {
+            const double g = __builtin_fma(12.0, f * (r2 * rinv), __builtin_fma(dv, sel, v1));
+            pe[u] += __builtin_fma(__builtin_fma(a, x6, b + b), x6, -g);
+          } else {
+            const auto& W = s_en[0];
+            const T s2 = W.sig2[ab] * r2i, s6 = s2 * s2 * s2;
+            pe[u] += W.c12[ab] * (s6 * s6) + W.c6[ab] * s6 - W.vc[ab] -
+                     (r2 * rinv - W.rc[ab]) * W.fs[ab];
+          }
           vw[u] += fr * r2;
         }
       }
@@ -411,7 +441,7 @@ __attribute__((amdgpu_waves_per_eu(EN || BIG || (!MIXED && TPP == 2) ? 4 : 6))) 
     double pi = 0.0, wi = 0.0;
     if constexpr (EN) {
       const bool on = h < nh && lp == 0;
-      pi = on ? 0.5 * (double)pe[0] : 0.0;
+      pi = on ? (NS == 2 ? 1.0 / 24.0 : 0.5) * (double)pe[0] : 0.0;
       wi = on ? 0.5 * (double)vw[0] : 0.0;
     }
 #pragma unroll
@@ -481,7 +511,8 @@ void launch_ns(hipStream_t s, int32_t mode, int32_t energy, int32_t tpp, int32_t
   // mode 0 (a plain force evaluation) always forms the energies
   if (mode == 0) { KT(0, true); }
   else if (mode == 1) { if (energy) { KT(1, true); } else { KT(1, false); } }
-  else { if (energy) { KT(2, true); } else { KT(2, false); } }
+  else if constexpr (!MIXED) { if (energy) { KT(2, true); } else { KT(2, false); } }
+  else { KT(2, false); }  // (mixed steps that form energies are not fused)
 #undef KT
 #undef KF
 }

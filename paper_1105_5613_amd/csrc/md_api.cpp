@@ -386,6 +386,14 @@ BrickPair brick_pair(const md_params& p, const PairTab& t) {
       split(b.msig2[a], t.sig2[k0], t.sig2[k1]);
       split(b.mf12[a], t.f12[k0], t.f12[k1]);
       split(b.mfs[a], t.fs[k0], t.fs[k1]);
+      // energies only, where the last bit of a constant does not matter
+      auto v12 = [&](int k) { return 12.0 * (t.vc[k] - t.rc[k] * t.fs[k]); };
+      b.v12[a][0] = v12(k0);
+      b.v12[a][1] = (v12(k1) - v12(k0)) * 0.5;
+      b.mrc[a][0] = (float)t.rc[k0];
+      b.mrc[a][1] = (float)t.rc[k1];
+      b.mv12[a][0] = (float)(12.0 * t.vc[k0]);
+      b.mv12[a][1] = (float)(12.0 * t.vc[k1]);
     }
     if (exact) {
       b.flip = flip;
@@ -967,6 +975,16 @@ int32_t energy_step_graph(const ThermoArgs& ta, int32_t k, int32_t K) {
 
 md_status reserve_events(md_ctx c, int32_t nsteps);
 
+// Whether directly launched step k also applies the next step's kick and drift.
+// Not the last step of a call, and on the tiles of the mixed form no step that
+// forms energies: that launch fused does not hold its registers at three blocks
+// per CU (logged every step, 1,048,576 particles: 301 us a step fused at two,
+// 276 not fused; FP64, two blocks either way: 326 against 343).
+bool fuses(md_ctx c, const ThermoArgs& ta, int32_t k, int32_t nsteps, bool fusable) {
+  return fusable && k + 1 < nsteps &&
+         !(c->brick && c->mixed && energy_step(ta, k, nsteps - 1));
+}
+
 // Directly launched steps [k0, nsteps) of an md_step call whose steps
 // [0, kg) ran inside graph replays.  A step launched here after another one
 // of this loop had its kick and drift applied by that step's force launch
@@ -978,11 +996,12 @@ md_status enqueue_direct(md_ctx c, hipStream_t s, const ThermoArgs& ta, int32_t 
                          int32_t k0, int32_t nsteps, bool fusable, bool resume, int32_t src) {
   md_status rc = reserve_events(c, nsteps - k0);
   if (rc) return rc;
+  bool fused = false;  // the step before
   for (int32_t k = k0; k < nsteps; ++k) {
-    const bool res = resume && k == k0;
-    const bool kick = !res && !(fusable && k > k0);
-    rc = enqueue_step(c, s, ta, thermo, k, energy_step(ta, k, nsteps - 1), kick,
-                      fusable && k + 1 < nsteps, res, res ? src : -1);
+    const bool res = resume && k == k0, kick = !res && !fused;
+    fused = fuses(c, ta, k, nsteps, fusable);
+    rc = enqueue_step(c, s, ta, thermo, k, energy_step(ta, k, nsteps - 1), kick, fused, res,
+                      res ? src : -1);
     if (rc) return rc;
   }
   return MD_OK;
@@ -1540,6 +1559,7 @@ md_status md_step(md_ctx c, int32_t nsteps, const double* T0, const double* T1,
   // a list build that overflowed halted the queued steps (kHalt): grow the
   // capacity, rebuild the interrupted step's lists on its state and finish
   // the call from there -- the trajectory of a context with enough capacity
+  int32_t at = -1, src = 0;
   for (int attempt = 0;; ++attempt) {
     HIPCHECK(c, hipStreamSynchronize(s));
     DevState st{};
@@ -1548,6 +1568,11 @@ md_status md_step(md_ctx c, int32_t nsteps, const double* T0, const double* T1,
     if (!(st.err & mend) || (st.err & ~mend) || attempt == 8) break;
     int64_t done = 0;
     HIPCHECK(c, hipMemcpy(&done, c->kcall, sizeof(int64_t), hipMemcpyDeviceToHost));
+    // how the interrupted step was queued: its kick by the step before or by
+    // itself; one that is interrupted again was queued as before
+    if ((int32_t)done != at)
+      src = (int32_t)done > kg && fuses(c, ta, (int32_t)done - 1, nsteps, fusable) ? 1 : 0;
+    at = (int32_t)done;
     if (st.err & kErrSlots) {
       rc = c->brick ? leave_brick(c) : leave_search(c);
     } else {
@@ -1563,11 +1588,9 @@ md_status md_step(md_ctx c, int32_t nsteps, const double* T0, const double* T1,
     st.err = 0;
     st.any_rebuild = 1;  // the interrupted step's rebuild flags are still set
     HIPCHECK(c, hipMemcpy(c->st, &st, sizeof(DevState), hipMemcpyHostToDevice));
-    // how the interrupted step was queued, and how the rest can be: the
-    // kernels a context goes on with may not fuse (row tiles)
-    const int32_t src = fusable && (int32_t)done > kg ? 1 : 0;
+    // the kernels that a context goes on with may not fuse (row tiles)
     fusable = can_fuse(c, thermo);
-    rc = enqueue_direct(c, s, ta, thermo, (int32_t)done, nsteps, fusable, true, src);
+    rc = enqueue_direct(c, s, ta, thermo, at, nsteps, fusable, true, src);
     if (rc) return rc;
     if (thermo)
       launch_apply_lambda(s, c->ntiles, c->tiles, c->stride, c->vel, c->lam, c->nrep, c->st);
