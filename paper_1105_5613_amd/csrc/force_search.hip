@@ -108,7 +108,11 @@ k_force_search(BrickArgs A, const RepDesc* __restrict__ reps, const PairTab* __r
   __shared__ uint32_t s_hits[kWaves][kWords * kGroup];      // [word][home]
   __shared__ uint32_t s_word[kWaves][kMeta * (kWords + 1)];  // first slot | slots << 16, species bits
   __shared__ double s_red[4][kWaves];
-  __shared__ typename std::conditional<EN, EnergyTab<T>, char>::type s_en[1];
+  __shared__ typename std::conditional<EN && (NS > 2), EnergyTab<T>, char>::type s_en[1];
+  // energy constants by home species and species bit (force_brick.hip): v12, or
+  // rc and 12 vc in the mixed form; one read per pair (the form with two species
+  // has no registers to spare)
+  __shared__ typename std::conditional<MIXED, float2, double>::type s_ev[EN && NS == 2 ? 8 : 1];
   __shared__ PairRow s_pair[NS > 2 ? 16 : 1];
   __shared__ double s_mass[4], s_im[4];
   static_assert(sizeof(TileRow) * kTileRows <= sizeof(s_hits), "rows share the words' LDS");
@@ -143,7 +147,15 @@ k_force_search(BrickArgs A, const RepDesc* __restrict__ reps, const PairTab* __r
   }
   if (threadIdx.x < 16) {
     const int k = threadIdx.x;
-    if constexpr (EN) {
+    if constexpr (EN && NS == 2) {
+      if (k < 8) {
+        if constexpr (MIXED)
+          s_ev[k] = make_float2(bp->mrc[k >> 1][k & 1], bp->mv12[k >> 1][k & 1]);
+        else
+          s_ev[k] = __builtin_fma(bp->v12[k >> 1][1], (k & 1) ? 2.0 : 0.0, bp->v12[k >> 1][0]);
+      }
+    }
+    if constexpr (EN && NS > 2) {
       s_en[0].sig2[k] = (T)tab->sig2[k];
       s_en[0].c12[k] = (T)tab->c12[k];
       s_en[0].c6[k] = (T)tab->c6[k];
@@ -475,15 +487,14 @@ k_force_search(BrickArgs A, const RepDesc* __restrict__ reps, const PairTab* __r
             const double r2d = __builtin_fma(ez, ez, __builtin_fma(ey, ey, ex * ex));
             // 2.0 or 0.0 from the species bit
             const double sel = __hiloint2double((int)(sp[u] << 30), 0);
-            const int32_t ab = NS > 2 ? 4 * ti + (int32_t)sp[u]
-                                      : 4 * ti + (sp[u] ? flip : 1 - flip);
+            const int32_t ab = NS > 2 ? 4 * ti + (int32_t)sp[u] : 0;
             double rc2;
             if constexpr (NS == 2)
               rc2 = __builtin_fma(drc, sel, rc1);
             else
               rc2 = s_pair[ab].rc2;
             if (r2d < rc2) {
-              T a, b, f, fr, rinv, r2i;
+              T a, b, f, fr, rinv, r2i, x6;  // x6: (s/r)^6 (mixed) or r^-6
               if constexpr (NS == 2) {
                 const T sl = MIXED ? (T)__int_as_float((int)(sp[u] << 30)) : (T)sel;
                 a = fma_t(da, sl, a1);
@@ -499,22 +510,33 @@ k_force_search(BrickArgs A, const RepDesc* __restrict__ reps, const PairTab* __r
               if constexpr (MIXED) {
                 rinv = __builtin_amdgcn_rsqf(r2);
                 r2i = rinv * rinv;
-                const float q2 = a * r2i, q6 = q2 * q2 * q2;
-                fr = b * (q6 - mk) * q6 * r2i + f * rinv;
+                const float q2 = a * r2i;
+                x6 = q2 * q2 * q2;
+                fr = b * (x6 - mk) * x6 * r2i + f * rinv;
               } else {
                 rinv = rsqrt3(r2d);
                 r2i = rinv * rinv;
-                const double r6 = r2i * r2i * r2i;
-                fr = __builtin_fma(__builtin_fma(a, r6, b) * r6, r2i, f * rinv);
+                x6 = r2i * r2i * r2i;
+                fr = __builtin_fma(__builtin_fma(a, x6, b) * x6, r2i, f * rinv);
               }
               fx = fma_t(fr, dx, fx);
               fy = fma_t(fr, dy, fy);
               fz = fma_t(fr, dz, fz);
               if constexpr (EN) {
-                const auto& W = s_en[0];
-                const T q2 = W.sig2[ab] * r2i, q6 = q2 * q2 * q2;
-                pe += W.c12[ab] * (q6 * q6) + W.c6[ab] * q6 - W.vc[ab] -
-                      (r2 * rinv - W.rc[ab]) * W.fs[ab];
+                if constexpr (NS == 2 && MIXED) {
+                  const float2 cv = s_ev[2 * ti + (int32_t)sp[u]];
+                  pe += __builtin_fmaf(-12.0f, (r2 * rinv - cv.x) * f,
+                                       __builtin_fmaf(b, (x6 - (mk + mk)) * x6, -cv.y));
+                } else if constexpr (NS == 2) {
+                  const double g =
+                      __builtin_fma(12.0, f * (r2 * rinv), s_ev[2 * ti + (int32_t)sp[u]]);
+                  pe += __builtin_fma(__builtin_fma(a, x6, b + b), x6, -g);
+                } else {
+                  const auto& W = s_en[0];
+                  const T q2 = W.sig2[ab] * r2i, q6 = q2 * q2 * q2;
+                  pe += W.c12[ab] * (q6 * q6) + W.c6[ab] * q6 - W.vc[ab] -
+                        (r2 * rinv - W.rc[ab]) * W.fs[ab];
+                }
                 vw += fr * r2;
               }
             }
@@ -526,7 +548,7 @@ k_force_search(BrickArgs A, const RepDesc* __restrict__ reps, const PairTab* __r
       fy += __shfl_xor(fy, 32, 64);
       fz += __shfl_xor(fz, 32, 64);
       if constexpr (EN) {
-        sum_pe += 0.5 * (double)pe;
+        sum_pe += (NS == 2 ? 1.0 / 24.0 : 0.5) * (double)pe;
         sum_w += 0.5 * (double)vw;
       }
       if (lane < gn) {
