@@ -51,6 +51,7 @@ struct BrickTile {
   int32_t units;        // partials of the tile: 1, or kTileUnits of kUnitHomes homes each
   int32_t part;         // its first partial
   int32_t b0, nb;       // its bricks
+  int32_t waves, groups;  // list-free search: waves that work, and how many share a brick
 };
 struct Brick {
   int32_t tile;

@@ -6,7 +6,9 @@
 //
 // One block per tile copies the tile's neighbourhood into LDS as there; a wave
 // takes one brick of home cells (1 x 1 x 1 at the Lennard-Jones density) at a
-// time, at most 32 home particles together.
+// time, at most 32 home particles together.  LDS allows two blocks per CU, so
+// that in tiles of fewer bricks than eight, whose cells are crowded, the groups
+// of a brick's homes go to several waves (plan_bricks).
 //
 // Search.  The candidates of a brick are, per neighbour row, one run of slots;
 // the runs are cut into pieces of at most 32 slots, the words of candidates,
@@ -238,7 +240,10 @@ k_force_search(BrickArgs A, const RepDesc* __restrict__ reps, const PairTab* __r
   const T mk = MIXED ? (T)bp->mk : (T)0;
   double sum_pe = 0.0, sum_w = 0.0, sum_ke = 0.0, d2 = 0.0;
 
-  for (int32_t bi = wv; bi < Tl.nb; bi += nw) {
+  // unit: a brick, or every Tl.groups-th group of its homes
+  const int32_t units = wv < Tl.waves ? Tl.nb * Tl.groups : 0;
+  for (int32_t un = wv; un < units; un += Tl.waves) {
+    const int32_t bi = un / Tl.groups, gfirst = un - bi * Tl.groups;
     const Brick B = A.bricks[Tl.b0 + bi];
     // lane q: the run of neighbour row q
     const int32_t by = B.hy + 2, nr = by * (B.hz + 2), nhr = B.hy * B.hz;
@@ -293,7 +298,7 @@ k_force_search(BrickArgs A, const RepDesc* __restrict__ reps, const PairTab* __r
     const int32_t ngrp = (nh + kGroup - 1) / kGroup;
     const int32_t gsz = ngrp ? (nh + ngrp - 1) / ngrp : 1;
     int32_t filled = -1;  // the pass whose pieces the tables hold
-    for (int32_t g0 = 0; g0 < nh; g0 += gsz) {
+    for (int32_t g0 = gfirst * gsz; g0 < nh; g0 += gsz * Tl.groups) {
       const int32_t gn = nh - g0 < gsz ? nh - g0 : gsz;
       // column hl: sorted index, slot and own candidate (32 piece + place)
       int32_t i = 0, slot = 0, own = 0;

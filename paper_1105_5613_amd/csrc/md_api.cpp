@@ -509,7 +509,7 @@ bool plan_bricks(md_ctx c) {
   c->brick_parts = 0;
   c->ba = BrickArgs{};
   bool big = false;
-  int32_t bricks = 1;  // most of a tile
+  int32_t waves = 1;  // of the search, most of a tile
   for (int32_t r = 0; r < c->nrep; ++r) {
     RepDesc& d = c->reps_h[r];
     const int32_t nc = d.nc;
@@ -527,11 +527,22 @@ bool plan_bricks(md_ctx c) {
       for (int y = 1; y <= by; ++y)
         for (int z = 1; z <= bz; ++z) {
           const double homes = ppc * x * y * z, cand = ppc * (x + 2) * (y + 2) * (z + 2);
+          // (the search has one wave per brick: as many as a tile has cells, up to eight)
+          const int32_t of_tile = ((bx + x - 1) / x) * ((by + y - 1) / y) * ((bz + z - 1) / z);
+          if (cells && of_tile < std::min(bx * by * bz, search_waves())) continue;
           const double cost = (std::ceil(cand * 1.02 / 64.0) + 3.0) *
                               std::ceil(1.08 * homes / 32.0) / homes;
           if (cost < best) best = cost, hx = x, hy = y, hz = z;
         }
     const double cand = ppc * (hx + 2) * (hy + 2) * (hz + 2);
+    // search in tiles of few, crowded bricks: several waves take a brick's
+    // groups of homes (a step of 1,048,576 particles mixed: 32 per cell, four
+    // bricks a tile, one wave each 1,307 us, two waves each 716; 43 per cell,
+    // one brick and one wave of two cells 2,925, two bricks of two waves 1,113;
+    // by row tiles 1,262 and 1,728)
+    const int32_t full = ((bx + hx - 1) / hx) * ((by + hy - 1) / hy) * ((bz + hz - 1) / hz);
+    const int32_t share = std::max(1, std::min((int32_t)std::ceil(1.08 * ppc * hx * hy * hz / 32.0),
+                                               search_waves() / full));
     c->ba.groups = std::max(c->ba.groups,
                             (int32_t)std::ceil(1.15 * ppc * hx * hy * hz / 32.0));
     c->brick_extra = std::max(c->brick_extra, (int32_t)(1.15 * cand / (64 * pass)));
@@ -588,7 +599,9 @@ bool plan_bricks(md_ctx c) {
                 c->bricks_h.push_back(b);
               }
           t.nb = (int32_t)c->bricks_h.size() - t.b0;
-          bricks = std::max(bricks, t.nb);
+          t.groups = share;
+          t.waves = std::min(t.nb * share, search_waves());
+          waves = std::max(waves, t.waves);
           c->btiles_h.push_back(t);
           c->ba.rows = std::max(c->ba.rows, (t.ty + 2) * (t.tz + 2));
           c->ba.hrows = std::max(c->ba.hrows, t.ty * t.tz);
@@ -608,7 +621,7 @@ bool plan_bricks(md_ctx c) {
     if (t.units == 1) c->ba.split = 1;
   c->brick = !cells;
   c->search = cells;
-  c->search_threads = 64 * std::min(bricks, search_waves());
+  c->search_threads = 64 * waves;
   return true;
 }
 
