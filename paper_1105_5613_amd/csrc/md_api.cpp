@@ -471,6 +471,13 @@ bool plan_bricks(md_ctx c) {
       return b.x * b.y * b.z;
     };
     if (fits(std::min(most, kBrickSlots)) < 8) fits(most);
+    // three cells a side: nine even tiles of one row of cells in the smaller
+    // layout instead of six to eight uneven ones in the larger (replicas of 1,000
+    // particles, per step, tiles of 3 x 2 x 1 -> so: 64 of them 93.0 -> 86.5 us,
+    // mixed 89.5 -> 84.0, 256: 148 -> 135 and 140 -> 130; by gathers 82, 81, 151
+    // and 131; 8: 40.9 -> 42.4, by gathers 73)
+    if (!cells && d.nc == 3 && slots(ppc, 3, 1, 1) < kBrickSlots)
+      b.x = 3, b.y = b.z = 1;
     b.big = slots(ppc, b.x, b.y, b.z) >= kBrickSlots;
     return b;
   };
