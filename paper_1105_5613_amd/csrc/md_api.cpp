@@ -1775,16 +1775,26 @@ md_status md_autotune(md_ctx c, int32_t reps, md_tune* out) {
   *out = md_tune{};
   double best = 1e300;
   int32_t btpp = c->tpp, bun = c->unroll;
+  // the form that the steps run (their registers differ): without energies, and
+  // fused with the next kick where NVE steps are (the thermostat's are not); its
+  // velocities and positions go to the scratch of the rebuild chain
+  const int32_t mode = can_fuse(c, 0) && c->p.graph_steps == 0 ? 2 : 1;
+  double* const vel = c->vel;
+  auto timed = [&](float* ms) {
+    c->vel = c->vel_tmp;
+    launch_forces(c, mode, c->stream, 0);  // warm
+    (void)hipEventRecord(e0, c->stream);
+    for (int r = 0; r < reps; ++r) launch_forces(c, mode, c->stream, 0);
+    (void)hipEventRecord(e1, c->stream);
+    c->vel = vel;
+    const hipError_t e = hipEventSynchronize(e1);
+    return e == hipSuccess ? hipEventElapsedTime(ms, e0, e1) : e;
+  };
   for (auto& tu : cand) {
     c->tpp = tu.first;
     c->unroll = tu.second;
-    launch_forces(c, 0, c->stream);  // warm
-    HIPCHECK(c, hipEventRecord(e0, c->stream));
-    for (int r = 0; r < reps; ++r) launch_forces(c, 0, c->stream);
-    HIPCHECK(c, hipEventRecord(e1, c->stream));
-    HIPCHECK(c, hipEventSynchronize(e1));
     float ms = 0.0f;
-    HIPCHECK(c, hipEventElapsedTime(&ms, e0, e1));
+    HIPCHECK(c, timed(&ms));
     const double avg = ms / reps;
     if (out->ntried < 16) {
       out->tried_tpp[out->ntried] = tu.first;
