@@ -42,34 +42,14 @@
 // home particles, so that results do not depend on TPP or the block size.
 #include <type_traits>
 
-#include "brick.h"
+#include "brick_device.h"
 
 namespace mdk {
 namespace {
 
 constexpr int kTaskHomes = 16;  // homes per partial of the energies
-constexpr double kFarAway = 1.0e300;
 constexpr int kAhead = 1;  // list chunks read ahead (2, 3 and 4 measured the same)
 static_assert(kAhead <= kChunksAhead, "chunk_elems allocates what is read ahead");
-
-template <typename T>
-struct EnergyTab {
-  T sig2[16], c12[16], c6[16], vc[16], fs[16], rc[16];
-};
-// species table of the four-species form
-struct PairRow {
-  double rc2, a, b, fs;
-  float sig2, f12, mfs, pad;
-};
-
-__device__ inline double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
-__device__ inline float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-
-__device__ inline double rsqrt3(double r2) {
-  const double y = __builtin_amdgcn_rsq(r2);
-  const double e = __builtin_fma(-r2 * y, y, 1.0);
-  return __builtin_fma(y * e, __builtin_fma(e, 0.375, 0.5), y);
-}
 
 // Registers: three blocks of eight waves fit a CU at 80 VGPRs, which the mixed
 // form holds without spills.  The FP64 form with two lanes per particle spills
@@ -116,17 +96,10 @@ __attribute__((amdgpu_waves_per_eu(BIG || (EN && NS > 2) || (!MIXED && (EN || TP
   if (threadIdx.x < 16) {
     const int k = threadIdx.x;
     if constexpr (EN && NS > 2) {
-      s_en[0].sig2[k] = (T)tab->sig2[k];
-      s_en[0].c12[k] = (T)tab->c12[k];
-      s_en[0].c6[k] = (T)tab->c6[k];
-      s_en[0].vc[k] = (T)tab->vc[k];
-      s_en[0].fs[k] = (T)tab->fs[k];
-      s_en[0].rc[k] = (T)tab->rc[k];
+      fill_energy(s_en[0], tab, k);
     }
     if constexpr (NS > 2) {
-      const double s2 = tab->sig2[k], s6 = s2 * s2 * s2;
-      s_pair[k] = PairRow{tab->rc2[k], tab->f12[k] * (s6 * s6), tab->f6[k] * s6, tab->fs[k],
-                          (float)s2, (float)tab->f12[k], (float)tab->fs[k], 0.0f};
+      s_pair[k] = pair_row(tab, k);
     }
   }
   if (threadIdx.x == 0) {
@@ -169,48 +142,8 @@ __attribute__((amdgpu_waves_per_eu(BIG || (EN && NS > 2) || (!MIXED && (EN || TP
     return m;
   };
   Home me = load_home(h0 + wv * kHomes + lane / TPP);
-  {
-    const double L = R.L;
-    const int32_t nc = R.nc;
-    // rows q and q + nw of a wave, 128 slots each, per round: four records in
-    // flight per lane
-    auto fetch = [&](int q, int32_t v, bool& on, double4& c) {
-      const TileRow w = s_row[q];
-      on = v < min(w.l3, kPadSlot);
-      int32_t j = w.gm + (v - w.l1);
-      if (v < w.l1) j = w.gl + (v - w.l0);
-      if (v >= w.l2) j = w.gr + (v - w.l2);
-      if (on) c = pos[j];
-    };
-    auto put = [&](int q, int32_t v, bool on, const double4& c) {
-      const int32_t y = Tl.cy + q % ry - 1, z = Tl.cz + q / ry - 1;
-      const double sy = y < 0 ? -L : (y >= nc ? L : 0.0), sz = z < 0 ? -L : (z >= nc ? L : 0.0);
-      const TileRow w = s_row[q];
-      const double sx = v < w.l1 ? -L : (v >= w.l2 ? L : 0.0);
-      if (on) {
-        s_xy[v] = make_double2(c.x + sx, c.y + sy);
-        s_z[v] = c.z + sz;
-      }
-    };
-    for (int q = wv; q < nr; q += 2 * nw) {
-      const int q2 = q + nw < nr ? q + nw : q;
-      const int32_t n = max(s_row[q].l3 - s_row[q].l0, s_row[q2].l3 - s_row[q2].l0);
-      for (int32_t t = lane; t < n; t += 128) {
-        bool on[4];
-        double4 c[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const int qk = k < 2 ? q : q2;
-          fetch(qk, s_row[qk].l0 + t + 64 * (k & 1), on[k], c[k]);
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const int qk = k < 2 ? q : q2;
-          put(qk, s_row[qk].l0 + t + 64 * (k & 1), on[k], c[k]);
-        }
-      }
-    }
-  }
+  copy_neighbourhood(Tl, R, s_row, pos, s_xy, s_z, kPadSlot, wv, nw, lane,
+                     [](int32_t, const double4&) {});
   __syncthreads();
 
   const size_t base = list_base(s_home[0].g, A.capc) & ~(size_t)(kSlice - 1);

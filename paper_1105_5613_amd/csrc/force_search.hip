@@ -36,60 +36,15 @@
 // instead of 2, words of two 16-slot pieces: 141 to 148 us).
 #include <type_traits>
 
-#include "brick.h"
+#include "brick_device.h"
 
 namespace mdk {
 namespace {
 
-constexpr double kFarAway = 1.0e300;
 constexpr float kWiden = 2.0e-5f;  // of the squared width of the brick
-constexpr float kNoHit = 1.0e4f;   // r^2 of the idle rows and columns, in squared cell sides
 constexpr int kWaves = 8;          // waves per block, at most (two blocks fit a CU)
-constexpr int kGroup = 32;         // home particles per group (columns of the product)
 constexpr int kPiece = 32;         // slots per word, at most
 constexpr int kUnroll = 2;         // pairs of a lane's walk in flight together
-
-using f32x16 = __attribute__((ext_vector_type(16))) float;
-
-// as in nlist_brick.hip
-__device__ inline void swap_halves(uint32_t& a, uint32_t& b) {
-  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
-  a = r[0];
-  b = r[1];
-}
-__device__ inline void swap_halves(float& a, float& b) {
-  uint32_t x = __float_as_uint(a), y = __float_as_uint(b);
-  swap_halves(x, y);
-  a = __uint_as_float(x);
-  b = __uint_as_float(y);
-}
-__device__ inline uint32_t sign_bits(const f32x16& w) {
-  uint32_t m = 0u;
-#pragma unroll
-  for (int r = 15; r >= 0; --r) m = __builtin_amdgcn_alignbit(m, __float_as_uint(w[r]), 31);
-  return m;
-}
-__device__ inline void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-__device__ inline double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
-__device__ inline float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-__device__ inline double rsqrt3(double r2) {
-  const double y = __builtin_amdgcn_rsq(r2);
-  const double e = __builtin_fma(-r2 * y, y, 1.0);
-  return __builtin_fma(y * e, __builtin_fma(e, 0.375, 0.5), y);
-}
-
-template <typename T>
-struct EnergyTab {
-  T sig2[16], c12[16], c6[16], vc[16], fs[16], rc[16];
-};
-struct PairRow {  // species table of the four-species form
-  double rc2, a, b, fs;
-  float sig2, f12, mfs, pad;
-};
 
 // NS = 2: at most two species, one bit per candidate; NS = 4: two.
 template <bool MIXED, int MODE, bool EN, int NS>
@@ -158,17 +113,10 @@ k_force_search(BrickArgs A, const RepDesc* __restrict__ reps, const PairTab* __r
       }
     }
     if constexpr (EN && NS > 2) {
-      s_en[0].sig2[k] = (T)tab->sig2[k];
-      s_en[0].c12[k] = (T)tab->c12[k];
-      s_en[0].c6[k] = (T)tab->c6[k];
-      s_en[0].vc[k] = (T)tab->vc[k];
-      s_en[0].fs[k] = (T)tab->fs[k];
-      s_en[0].rc[k] = (T)tab->rc[k];
+      fill_energy(s_en[0], tab, k);
     }
     if constexpr (NS > 2) {
-      const double s2 = tab->sig2[k], s6 = s2 * s2 * s2;
-      s_pair[k] = PairRow{tab->rc2[k], tab->f12[k] * (s6 * s6), tab->f6[k] * s6, tab->fs[k],
-                          (float)s2, (float)tab->f12[k], (float)tab->fs[k], 0.0f};
+      s_pair[k] = pair_row(tab, k);
     }
   }
   if (threadIdx.x == 0) {
@@ -179,56 +127,16 @@ k_force_search(BrickArgs A, const RepDesc* __restrict__ reps, const PairTab* __r
   const int32_t nc = R.nc;
   const int32_t flip = bp->flip;
   __syncthreads();
-  {
-    const double L = R.L;
-    // rows q and q + nw of a wave, 128 slots each, per round: four records in
-    // flight per lane
-    auto fetch = [&](int q, int32_t v, bool& on, double4& c) {
-      const TileRow w = s_row[q];
-      on = v < min(w.l3, kPadSlot);
-      int32_t j = w.gm + (v - w.l1);
-      if (v < w.l1) j = w.gl + (v - w.l0);
-      if (v >= w.l2) j = w.gr + (v - w.l2);
-      if (on) c = pos[j];
-    };
-    auto put = [&](int q, int32_t v, bool on, const double4& c) {
-      const int32_t y = Tl.cy + q % ry - 1, z = Tl.cz + q / ry - 1;
-      const double sy = y < 0 ? -L : (y >= nc ? L : 0.0), sz = z < 0 ? -L : (z >= nc ? L : 0.0);
-      const TileRow w = s_row[q];
-      const double sx = v < w.l1 ? -L : (v >= w.l2 ? L : 0.0);
-      if (on) {
-        s_xy[v] = make_double2(c.x + sx, c.y + sy);
-        s_z[v] = c.z + sz;
-        const int32_t tj = (int32_t)c.w;
-        if constexpr (NS > 2) {
-          if (tj & 1) atomicOr(&s_sp[0][v >> 5], 1u << (v & 31));
-          if (tj & 2) atomicOr(&s_sp[1][v >> 5], 1u << (v & 31));
-        } else {
-          if (tj == flip) atomicOr(&s_sp[0][v >> 5], 1u << (v & 31));
-        }
-      }
-    };
-    for (int q = wv; q < nrow; q += 2 * nw) {
-      const int q2 = q + nw < nrow ? q + nw : q;
-      const bool two = q2 != q;
-      const int32_t n = max(s_row[q].l3 - s_row[q].l0, s_row[q2].l3 - s_row[q2].l0);
-      for (int32_t t = lane; t < n; t += 128) {
-        bool on[4];
-        double4 c[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const int qk = k < 2 ? q : q2;
-          fetch(qk, s_row[qk].l0 + t + 64 * (k & 1), on[k], c[k]);
-          if (k >= 2) on[k] = on[k] && two;
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const int qk = k < 2 ? q : q2;
-          put(qk, s_row[qk].l0 + t + 64 * (k & 1), on[k], c[k]);
-        }
-      }
+  copy_neighbourhood(Tl, R, s_row, pos, s_xy, s_z, kPadSlot, wv, nw, lane,
+                     [&](int32_t v, const double4& c) {
+    const int32_t tj = (int32_t)c.w;
+    if constexpr (NS > 2) {
+      if (tj & 1) atomicOr(&s_sp[0][v >> 5], 1u << (v & 31));
+      if (tj & 2) atomicOr(&s_sp[1][v >> 5], 1u << (v & 31));
+    } else {
+      if (tj == flip) atomicOr(&s_sp[0][v >> 5], 1u << (v & 31));
     }
-  }
+  });
   __syncthreads();  // the rows' LDS holds words from here on
 
   uint32_t* const hits = s_hits[wv];

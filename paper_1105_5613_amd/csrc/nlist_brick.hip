@@ -38,14 +38,13 @@
 // search of nlist.hip writing 32-bit entries takes 550 us.
 #include <type_traits>
 
-#include "brick.h"
+#include "brick_device.h"
 
 #pragma clang fp contract(off)
 
 namespace mdk {
 namespace {
 
-constexpr int kNbGroup = 32;    // home particles per group (columns of the product)
 // Candidate chunks per pass.  A 1 x 1 x 1 brick of cells 2.8 to 3 wide
 // (replicas that need the larger LDS layout) has up to 14 chunks of
 // candidates: with 12 it took two passes (64 replicas of 1,000 to 65,536, a
@@ -56,32 +55,6 @@ constexpr int kNbWaves = 4;     // bricks per block
 constexpr int kCoopWaves = 8;   // waves per brick (COOP)
 constexpr int kCoopBlocks = 1024;  // most blocks of the COOP form
 constexpr float kUnclear = 1.0e-5f;
-constexpr float kNoHit = 1.0e4f;  // r^2 of the idle rows and columns, in squared cell sides
-
-using f32x16 = __attribute__((ext_vector_type(16))) float;
-
-// a = [a.lo, b.lo], b = [a.hi, b.hi] of the wave's halves: one value per
-// candidate of a chunk in each of two registers becomes the two k-slices of
-// the matrix operand for its first and its last 32 candidates.
-__device__ inline void swap_halves(uint32_t& a, uint32_t& b) {
-  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
-  a = r[0];
-  b = r[1];
-}
-__device__ inline void swap_halves(float& a, float& b) {
-  uint32_t x = __float_as_uint(a), y = __float_as_uint(b);
-  swap_halves(x, y);
-  a = __uint_as_float(x);
-  b = __uint_as_float(y);
-}
-
-// Sign bits of a lane's 16 results: bit r = result r below zero.
-__device__ inline uint32_t sign_bits(const f32x16& w) {
-  uint32_t m = 0u;
-#pragma unroll
-  for (int r = 15; r >= 0; --r) m = __builtin_amdgcn_alignbit(m, __float_as_uint(w[r]), 31);
-  return m;
-}
 
 // (This file is compiled with -fno-honor-nans: the results hold no NaN, as
 // positions are finite after the wrap, and the minimum needs no quieting of
@@ -92,12 +65,6 @@ __device__ inline float least_magnitude(const f32x16& w) {
   for (int r = 0; r < 16; r += 2)
     least = __builtin_fminf(__builtin_fminf(__builtin_fabsf(w[r]), __builtin_fabsf(w[r + 1])), least);
   return least;
-}
-
-__device__ inline void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 __device__ inline uint32_t image_code(int32_t sx, int32_t sy, int32_t sz) {
@@ -135,7 +102,7 @@ k_nlist_brick(BrickArgs A, const RepDesc* __restrict__ reps, const int32_t* __re
   __shared__ uint32_t s_kc[kB][CH * 64];  // sorted index | image code
   __shared__ uint16_t s_ent[kB][CH * 64];  // list entry
   // [word][home], a spare row before and after a wave's
-  __shared__ uint32_t s_hits[kB][(2 * CH + 2) * kNbGroup];
+  __shared__ uint32_t s_hits[kB][(2 * CH + 2) * kGroup];
   if (!st->any_rebuild) return;  // whole block: one flag load when nothing rebuilds
   if (threadIdx.x < 16) s_thr[threadIdx.x] = tab->thr[threadIdx.x];
   __syncthreads();
@@ -160,7 +127,7 @@ k_nlist_brick(BrickArgs A, const RepDesc* __restrict__ reps, const int32_t* __re
   const int32_t nc = R.nc;
   uint32_t* const kc = s_kc[COOP ? 0 : wv];
   uint16_t* const ent = s_ent[COOP ? 0 : wv];
-  uint32_t* const hits = s_hits[COOP ? 0 : wv] + kNbGroup;
+  uint32_t* const hits = s_hits[COOP ? 0 : wv] + kGroup;
 
   // lane q: row q of the cells around the brick, as up to three pieces
   const int32_t ry = B.hy + 2, nr = ry * (B.hz + 2), nhr = B.hy * B.hz;
@@ -227,7 +194,7 @@ k_nlist_brick(BrickArgs A, const RepDesc* __restrict__ reps, const int32_t* __re
   // in squared lengths from here on
   const float side2 = (float)(R.cside * R.cside);
   const float unclear = kUnclear * (float)(width * width) * side2, no_hit = kNoHit * side2;
-  const int hl = lane & (kNbGroup - 1), seg = lane >> 5;
+  const int hl = lane & (kGroup - 1), seg = lane >> 5;
   const double fsp = (double)flip;
   // the candidate of a chunk that this lane loads: result register r of lane
   // l is matrix row 8 (r / 4) + 4 (l / 32) + r % 4, so that row 8 a + 4 b + c
@@ -235,8 +202,8 @@ k_nlist_brick(BrickArgs A, const RepDesc* __restrict__ reps, const int32_t* __re
   // in order
   const int cofs = (lane & 32) + ((lane >> 2) & 1) * 16 + ((lane >> 3) & 3) * 4 + (lane & 3);
 
-  // groups of at most kNbGroup home particles, of equal size
-  const int32_t ngrp = (nh + kNbGroup - 1) / kNbGroup;
+  // groups of at most kGroup home particles, of equal size
+  const int32_t ngrp = (nh + kGroup - 1) / kGroup;
   const int32_t gsz = ngrp ? (nh + ngrp - 1) / ngrp : 1;
   // (the replica's own, not the context's: the order of its rows depends on it)
   const int32_t pass = 64 * (CH > kNbChunks ? min((int32_t)B.pass, CH) : CH);
@@ -416,7 +383,7 @@ k_nlist_brick(BrickArgs A, const RepDesc* __restrict__ reps, const int32_t* __re
           auto next = [&]() {
             f = __builtin_ctz(m);
             m &= m - 1u;
-            const uint32_t x = hits[(back ? nwords - 1 - f : f) * kNbGroup + hl];
+            const uint32_t x = hits[(back ? nwords - 1 - f : f) * kGroup + hl];
             cur = back ? __builtin_bitreverse32(x) : x;
           };
           for (next(); (int32_t)__popc(cur) <= rank; next()) rank -= (int32_t)__popc(cur);
