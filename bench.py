@@ -397,6 +397,20 @@ def _counter_rows(d, name_part):
     return out
 
 
+def _in_step(rows, counters, keyword=""):
+    """Values per counter of the kernel with the most dispatches among those whose
+    name holds keyword: the variant that the steps run.  The tuner launches the
+    others in the same form, a few times each."""
+    names = {}
+    for (k, c), vs in rows.items():
+        if keyword in k and c in counters:
+            names[k] = max(names.get(k, 0), len(vs))
+    if not names:
+        return {}
+    best = max(names, key=names.get)
+    return {c: rows[best, c] for c in counters if (best, c) in rows}
+
+
 def fp64_ops_summary(args):
     """FP64 operation counts (SQ_INSTS_VALU_{ADD,MUL,FMA,TRANS}_F64, wave
     instructions per dispatch) of the kernels in FLOP_KERNELS, averaged over
@@ -404,11 +418,9 @@ def fp64_ops_summary(args):
     out = {"commands": args.commands, "particles": args.n, "kernels": {}}
     for key, (frag, src) in FLOP_KERNELS.items():
         rows = _counter_rows(args.flops_dir, frag)
-        per = {}
-        for (k, c), vs in rows.items():
-            per.setdefault(c, []).extend(vs)
         need = ["SQ_INSTS_VALU_ADD_F64", "SQ_INSTS_VALU_MUL_F64", "SQ_INSTS_VALU_FMA_F64",
                 "SQ_INSTS_VALU_TRANS_F64"]
+        per = _in_step(rows, need)
         if not all(c in per for c in need):
             continue
         # dispatches that did work (a gated launch counts next to nothing)
@@ -428,8 +440,7 @@ def counters_summary(args):
     """FETCH_SIZE / WRITE_SIZE (KiB per dispatch) of the in-step force kernels,
     scaled by what the same counters read for the plain copy."""
     def mean_for(d, kern, counter, keyword):
-        rows = _counter_rows(d, kern)
-        vals = [v for (k, c), vs in rows.items() if c == counter and keyword in k for v in vs]
+        vals = _in_step(_counter_rows(d, kern), [counter], keyword).get(counter, [])
         return sum(vals) / len(vals), len(vals)
 
     cf, _ = mean_for(args.copy_fetch_dir, "", "FETCH_SIZE", "copy")

@@ -7,12 +7,14 @@
 //
 // Why LDS: a gather from memory costs one L1 tag access per lane and 16 bytes
 // and runs at one per cycle and CU, which bounded the gather kernel (force.hip)
-// at 264 us per launch for 1,048,576 particles (list radius 2.8, 92 entries);
+// at 261 us per launch for 1,048,576 particles (list radius 2.8, 92 entries);
 // random 8- and 16-byte LDS reads of a whole wave take about 9 ns together
 // (one ds_read_b128 for x and y, one ds_read_b64 for z; three b64: 14 ns),
-// 60 us per launch.  What bounds this kernel is vector issue: an FP64
-// instruction of a wave takes 2.05 ns, an FP32 or integer one 1.3 ns, 1/sqrt
-// 7.4 ns, so the arithmetic below is kept short:
+// 60 us per launch.  What bounds this kernel is vector issue: of a SIMD's time
+// an FP64 instruction of a wave and an FP32 one of three operands take 1.8 to
+// 2.1 ns, a 32-bit one of two operands 1.0 to 1.3 ns, 1/sqrt 7 ns, and the
+// vector units issue in 0.64 of the launch (mixed: 0.88; LDS is busy in 0.29 of
+// it, 0.40), so the arithmetic below is kept short:
 //  - the entry is the LDS byte offset, the species bit lands in the exponent
 //    of a double (2.0 or 0.0) with one AND, and each species constant is one
 //    FMA, p1 + d * 2, exact by choice of the base (BrickPair);
@@ -26,8 +28,11 @@
 //    overflow, it is tested).
 // (BIG: contexts with wider cells take 3,072 slots, two blocks per CU.)
 // Tiles of 2 x 2 x 2 cells (213 homes, 1,709 slots at rho = 1.2) put three
-// blocks of eight waves on a CU (51 KB of LDS each).  Measured per launch at
-// 1,048,576 particles, gather -> brick: FP64 264 -> 198 us, mixed 193 -> 145 us.
+// blocks of eight waves on a CU (51 KB of LDS each).  Measured per launch of
+// an NVE step (with the next step's kick and drift) at 1,048,576 particles,
+// gather with its best variant -> here: in the liquid (after 400 steps) FP64
+// 261 -> 202 us, mixed 182 -> 146 us; over the first 25 steps from the lattice,
+// whose rows are of more uneven length, 270 -> 222 and 189 -> 166 us.
 //
 // Energies come from what the force has formed, with one constant more per
 // species pair in FP64 and two in the mixed form (BrickPair), from registers;
@@ -54,7 +59,7 @@ static_assert(kAhead <= kChunksAhead, "chunk_elems allocates what is read ahead"
 // Registers: three blocks of eight waves fit a CU at 80 VGPRs, which the mixed
 // form holds without spills.  The FP64 form with two lanes per particle spills
 // there (203 us per NVE launch at 1,048,576 particles) and runs two blocks at
-// 96 without (198 us; four lanes at 80 VGPRs: 230 us).
+// 96 without (198 us in the same run; four lanes at 80 VGPRs: 11 % slower).
 template <bool MIXED, int MODE, int TPP, bool EN, int NS, bool BIG>
 __global__ __launch_bounds__(kBrickThreads)
 __attribute__((amdgpu_waves_per_eu(BIG || (EN && NS > 2) || (!MIXED && (EN || TPP == 2)) ? 4 : 6))) void k_force_brick(

@@ -23,14 +23,16 @@
 //
 // Evaluation.  The two lanes of a home walk the set bits of its words, one from
 // the first hit on and one from the last back, the same number each; a word
-// comes with its first slot and the species bits of its candidates.  The two sums of a home are added at the end.
+// comes with its first slot and the species bits of its candidates.  The two
+// sums of a home are added at the end.
 //
-// What bounds it: vector issue at four waves per SIMD, which LDS allows (62
-// pairs per particle in the evaluation, half of the time at 1.3 to 2 ns per
-// instruction; the sign bits and operands of the search), and the waves' wait
-// for the copy to LDS.  The form before this (force_cells.hip: one lane per home, candidates
-// through the scalar cache) tests every candidate in FP64, 720 per particle,
-// and stays for row tiles asked for and for boxes too dense for the tiles.
+// What bounds it: vector issue (in 0.68 of a launch of 1,048,576 particles,
+// 400 us) at four waves per SIMD, which LDS allows (62 pairs per particle in
+// the evaluation, half of the time at 1 to 2 ns per instruction; the sign bits
+// and operands of the search), and the waves' wait for the copy to LDS.  The
+// form before this (force_cells.hip: one lane per home, candidates through the
+// scalar cache) tests every candidate in FP64, 720 per particle, and stays for
+// row tiles asked for and for boxes too dense for the tiles.
 // Measured per launch at 262,144 particles FP64: 526 -> 142 us, the search 65
 // and the evaluation 38 of it (reading candidates ahead, 4 pairs in flight
 // instead of 2, words of two 16-slot pieces: 141 to 148 us).

@@ -1264,8 +1264,8 @@ md_status md_init_alloc(md_ctx* out, const md_params* p, int32_t nrep, const int
   } else if (plan_bricks(c)) {
     // lanes per particle: four fill the chip sooner (per NVE launch 32,000
     // particles FP64 24 us against 33 with two, 131,072: 42 us both), two
-    // walk large boxes faster (1,048,576: 211 against 230 us, mixed 160
-    // against 190); results do not depend on it
+    // walk large boxes faster (1,048,576: 202 against 223 us, mixed 146
+    // against 184); results do not depend on it
     c->tpp = ntot < 200000 ? 4 : 2;
     c->unroll = kChunkEntries / c->tpp;
   } else {
