@@ -297,8 +297,9 @@ md_status md_profile_read(md_ctx ctx, md_prof* out);
 
 /* Autotuner: times every force-kernel variant of the context's path (lanes
  * per particle x unroll) on the current state, `reps` launches each of the form
- * that a step without energies runs, with hipEvents on the context stream, keeps
- * the fastest and recomputes forces and observables with it.
+ * that a step without energies runs (under the thermostat if the last md_step
+ * call was), with hipEvents on the context stream, keeps the fastest and
+ * recomputes forces and observables with it.
  * Positions and velocities are not changed.  Synchronises. */
 typedef struct {
   int32_t tpp, unroll;   /* chosen variant */
