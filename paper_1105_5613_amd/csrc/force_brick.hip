@@ -13,7 +13,7 @@
 // 60 us per launch.  What bounds this kernel is vector issue: of a SIMD's time
 // an FP64 instruction of a wave and an FP32 one of three operands take 1.8 to
 // 2.1 ns, a 32-bit one of two operands 1.0 to 1.3 ns, 1/sqrt 7 ns, and the
-// vector units issue in 0.64 of the launch (mixed: 0.88; LDS is busy in 0.29 of
+// vector units issue in 0.63 of the launch (mixed: 0.87; LDS is busy in 0.29 of
 // it, 0.40), so the arithmetic below is kept short:
 //  - the entry is the LDS byte offset, the species bit lands in the exponent
 //    of a double (2.0 or 0.0) with one AND, and each species constant is one
@@ -30,9 +30,9 @@
 // Tiles of 2 x 2 x 2 cells (213 homes, 1,709 slots at rho = 1.2) put three
 // blocks of eight waves on a CU (51 KB of LDS each).  Measured per launch of
 // an NVE step (with the next step's kick and drift) at 1,048,576 particles,
-// gather with its best variant -> here: in the liquid (after 400 steps) FP64
-// 261 -> 202 us, mixed 182 -> 146 us; over the first 25 steps from the lattice,
-// whose rows are of more uneven length, 270 -> 222 and 189 -> 166 us.
+// gather with its best variant -> here: after 400 steps FP64 261 -> 202 us,
+// mixed 182 -> 146 us; in the first 25 launches of a process, before the card
+// has raised its clocks, 270 -> 222 and 189 -> 166 us.
 //
 // Energies come from what the force has formed, with one constant more per
 // species pair in FP64 and two in the mixed form (BrickPair), from registers;

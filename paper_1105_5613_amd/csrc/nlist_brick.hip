@@ -34,11 +34,11 @@
 // the row's end point at the far slot (a search of several passes
 // ends each pass like that).
 //
-// Bound by vector issue (0.63 of the launch; the matrix cores work in 0.23 of
+// Bound by vector issue (0.69 of the launch; the matrix cores work in 0.26 of
 // it): the sign bits, the operands and the walk of the write phase.  Measured
 // at 1,048,576 particles (LJ box, list radius 2.8): 290 us; the VALU search of
-// nlist.hip writing 32-bit entries takes 491 us (both in the liquid; in the
-// first steps from the lattice 316 and 530).
+// nlist.hip writing 32-bit entries takes 491 us (in the first steps of a
+// process, at lower clocks, 316 and 530).
 #include <type_traits>
 
 #include "brick_device.h"
