@@ -959,8 +959,8 @@ md_status enqueue_step(md_ctx c, hipStream_t s, const ThermoArgs& ta, int32_t th
   const int32_t nzero = zero_in_kick ? c->ncells : 0;
   if (kick && !resume)
     launch_kick_drift(s, c->mixed, thermo, c->ntiles, c->tiles, c->reps, c->tab, c->pos,
-                      c->brick ? nullptr : c->pos16, c->vel, c->frc, c->xref, c->stride, c->p.dt, c->lam, c->rebuild,
-                      c->dmax, c->st, c->counts, nzero);
+                      c->brick ? nullptr : c->pos16, c->vel, c->frc, c->xref, c->stride, c->p.dt,
+                      c->lam, c->rebuild, c->dmax, c->st, c->counts, nzero);
   run_chain(c, s, zero_in_kick && !resume);
   const bool timed = c->prof_every > 0 && (k + 1) % c->prof_every == 0;
   if (timed) {
